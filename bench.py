@@ -50,14 +50,17 @@ SCLK_HZ = 2.4e9
 VALU_PEAK = N_CU * LANES_PER_CU_CLOCK * SCLK_HZ            # 39.32e12 lane-ops/s
 HBM_PEAK = 8.0e12                                           # B/s
 
-# Least VALU work per candidate of any exhaustive search: divided by the
-# request's Lout, a candidate's energy is Pp * (TTFT / Lout) + Pd * TBT, one fused
-# multiply-add of a request term and two GPU terms, and a three-way min folds two
-# candidates into the running minimum, half an instruction each.  SLO masks, power terms,
-# the per-request scale and the index of the winner are shared or recovered once per
-# request or GPU, so they are not counted.  The count runs over distinct candidates: the
-# cells of a capped GPU above max(cap_pf, cap_dc) repeat lower cells and need no work.
+# Least VALU work per candidate of an exhaustive search: divided by the request's Lout, a
+# candidate's energy is Pp * (TTFT / Lout) + Pd * TBT, one fused multiply-add of a request
+# term and two GPU terms, and a three-way min folds two candidates into the running minimum,
+# half an instruction each.  The count runs over distinct candidates: the cells of a capped
+# GPU above max(cap_pf, cap_dc) repeat lower cells and need no work.
 OPS_PER_CANDIDATE = 1.5
+# Least VALU work per (request, cell) of the front search (8 x 16 tables), which keeps only the
+# candidates of a cell that no other one dominates, at least one: the latency's SLO test, its
+# scale by 1 / Lout and its mask, then a fused multiply-add and half a three-way min for one
+# candidate.  The fronts and the index of the winner are shared or recovered once per request.
+OPS_PER_CELL = 4.5
 # Migration pair: two budget compares, level-mask AND and test, self test, lowest set bit,
 # u_s + u_d, two multiplies, subtract, FMA, compare with the best, three selects.
 OPS_PER_PAIR = 15
@@ -65,6 +68,7 @@ OPS_PER_PAIR = 15
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_score_config4_traffic.json")
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_score_config4_counters.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_2606_30391_amd", "csrc", "festina.hip")
+FRONTS_SRC = os.path.join(ROOT, "paper_2606_30391_amd", "csrc", "fronts.hip")
 SWEEP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_traffic.json")
 SWEEP_SRC = os.path.join(ROOT, "paper_2606_30391_amd", "csrc", "sweep.hip")
 TRANSFER_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_transfer_costs_traffic.json")
@@ -130,6 +134,14 @@ def placement_candidates(inp, sel=None):
     return int(hosts[model[ok]].sum()) * lut["n_sm"] * lut["n_freq"]
 
 
+def placement_ops(inp):
+    """Least VALU lane-operations of the search that serves these tables."""
+    lut = inp["lut"]
+    if lut["n_sm"] == 8 and lut["n_freq"] == 16:
+        return inp["requests"]["n_requests"] * 128 * OPS_PER_CELL
+    return distinct_candidates(inp) * OPS_PER_CANDIDATE
+
+
 def distinct_candidates(inp):
     """Candidates that are not repeats: a capped GPU's SM levels above max(cap_pf, cap_dc)
     repeat that level's cells exactly at a higher index (never the lowest-index minimum), so
@@ -183,7 +195,7 @@ def src_hash(path=KERNEL_SRC):
     return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
 
 
-def load_traffic(path=TRAFFIC_FILE, src=KERNEL_SRC):
+def load_traffic(path=TRAFFIC_FILE, src=FRONTS_SRC):
     """HBM bytes per launch of a kernel from the committed counter runs, or None when
     the kernel source changed since they were taken."""
     try:
@@ -195,7 +207,7 @@ def load_traffic(path=TRAFFIC_FILE, src=KERNEL_SRC):
     return d.get("hbm_bytes_per_launch")
 
 
-def load_counters(path=COUNTERS_FILE, src=KERNEL_SRC):
+def load_counters(path=COUNTERS_FILE, src=FRONTS_SRC):
     """VALU issue figures of the scoring kernel from the committed counter run, or None when
     the kernel source changed since it was taken."""
     try:
@@ -633,7 +645,8 @@ def main():
 
     step_s = (t1 - t0) / K
     value = (n_cand + n_pairs) / step_s
-    achieved = n_distinct * OPS_PER_CANDIDATE / (score_ms * 1e-3)
+    ops = placement_ops(place)
+    achieved = ops / (score_ms * 1e-3)
     gpu_place = dp.results()
     gpu_mig = dm.results()
 
@@ -664,14 +677,14 @@ def main():
             "parallelism": "single GPU",
         },
         "roofline": {
-            "kernel": "k_score (placement scoring + fused argmin)",
+            "kernel": "k_choose (placement scoring against the candidate fronts + fused argmin)",
             "bound": "alu",
             "achieved": achieved / 1e12,
             "peak": VALU_PEAK / 1e12,
             "unit": "T VALU lane-ops/s",
             "frac": achieved / VALU_PEAK,
             "traffic": load_traffic(),
-            "ops_per_candidate": OPS_PER_CANDIDATE,
+            "ops_per_candidate": ops / n_distinct,
             "candidates_counted": "distinct (capped GPUs' repeated SM levels excluded)",
             "kernel_ms": score_ms,
             "hbm_frac_algorithmic": placement_bytes(place) / (score_ms * 1e-3) / HBM_PEAK,
@@ -763,7 +776,7 @@ def per_config(F, W, hip, torch, verbose=False):
             inp = W.make_placement(cfg)
             dev = F.DevicePlacement(inp, "cuda")
             work = placement_candidates(inp)
-            ops = distinct_candidates(inp) * OPS_PER_CANDIDATE
+            ops = placement_ops(inp)
         else:
             inp = W.make_fleet()
             dev = F.DeviceMigration(inp, "cuda")
@@ -793,7 +806,7 @@ def per_config(F, W, hip, torch, verbose=False):
         for e in ev:
             hip.destroy(e)
         cm, km = float(np.median(call_ms)), float(np.median(kern_ms))
-        timed = "k_score (HIP events around the kernel inside the library)"
+        timed = "scoring kernel (HIP events around it inside the library)"
         if cfg == 5:
             # an event between the two migration kernels costs several microseconds of stream
             # time, more than the kernel itself: time a batch of whole calls instead

@@ -12,8 +12,9 @@ import subprocess
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", n) for n in ("festina.hip", "sweep.hip", "preferred.hip", "dispatch.hip",
-                                                       "transfer.hip")]
+SRCS = [os.path.join(HERE, "csrc", n) for n in ("festina.hip", "fronts.hip", "sweep.hip", "preferred.hip",
+                                                       "dispatch.hip", "transfer.hip")]
+HDRS = [os.path.join(HERE, "csrc", "fronts.h")]
 LIB = os.path.join(HERE, "libfestina.so")
 HASH_FILE = LIB + ".sources"
 HEADER = os.path.join(ROOT, "include", "festina.h")
@@ -25,9 +26,9 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
 
 
 def source_hash() -> str:
-    """SHA-256 over the library's sources, the public header and the compiler flags."""
+    """SHA-256 over the library's sources, its headers and the compiler flags."""
     h = hashlib.sha256()
-    for path in (*SRCS, HEADER):
+    for path in (*SRCS, *HDRS, HEADER):
         with open(path, "rb") as f:
             h.update(os.path.basename(path).encode() + b"\0" + f.read() + b"\0")
     h.update(" ".join(HIPCC_FLAGS[:-2]).encode())   # the include path is left out: it names the tree

@@ -1,6 +1,8 @@
 // festina.hip -- MI355X (gfx950) kernels and C-ABI host dispatch of the batched
 // energy-aware placement and migration search (Festina, Sec. 3.3 and Sec. 3.5).
 //
+// Placement searches of 8 x 16 tables with enough requests per (wave, model) go to the front
+// search in fronts.hip (the rule is festina_fronts::layout); all others run here:
 // Placement pipeline (one call, four launches on the caller's stream, five with k_scan):
 //   k_init      clear the bucket counters; the table minima (least entry of each prefill
 //                 row, its least nonzero magnitude, least decode entry of each model)
@@ -37,6 +39,7 @@
 #include <mutex>
 
 #include "festina.h"
+#include "fronts.h"
 
 namespace {
 
@@ -2103,6 +2106,8 @@ struct PlaceLayout {
   bool fast;                     // 8 SM x 16 frequency levels: the specialised kernel
   bool scan_local;               // k_scatter scans the bucket counts (no k_scan launch)
   size_t scatter_lds;            // dynamic LDS bytes of k_scatter
+  bool fronts;                   // the front search (fronts.hip) serves the call, with its own
+  festina_fronts::Layout front;  // workspace layout
 };
 
 bool place_shapes_ok(const festina_lut *L, const festina_gpus *G, const festina_requests *Q) {
@@ -2188,6 +2193,10 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
   const long long scan_ints = block_scan_ints(NB, ng, gpad > 1);
   o->scan_local = NB <= kHistMax && scan_ints <= kScanLds;
   o->scatter_lds = o->scan_local ? sizeof(int32_t) * (size_t)scan_ints : 0;
+  o->fronts = festina_fronts::layout(L, G, Q, &o->front);
+  // (the size stays at least the other kernels', so that festina_score_placements_noalloc takes
+  // and refuses the same shapes whichever search serves them)
+  if (o->fronts && o->front.total > o->total) o->total = o->front.total;
   return true;
 }
 
@@ -2254,6 +2263,7 @@ festina_status place_args(const festina_lut *L, const festina_gpus *G, const fes
 festina_status place_launch(const festina_lut *L, const festina_gpus *G, const festina_requests *Q,
                             const festina_placements *out, const PlaceLayout &lay, char *ws, void *stream,
                             void *ev_begin = nullptr, void *ev_end = nullptr) {
+  if (lay.fronts) return festina_fronts::launch(L, G, Q, out, lay.front, ws, stream, ev_begin, ev_end);
   const long long C = (long long)L->n_sm * L->n_freq;
   PlaceArgs a;
   a.M = L->n_models;

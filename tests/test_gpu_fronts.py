@@ -1,0 +1,144 @@
+"""GPU parity of the front search (8 x 16 tables), at the sizes and inputs where its steps change:
+chunks of requests and of hosts, fronts longer than a bucket's steps (built in the pool, or not
+at all), requests and tables that are scored against every GPU, groups that share a sort slot,
+and the shapes on either side of the rule that sends a call to it.
+
+Flags and indices must match the oracle exactly and energies within 1e-5; a different index is
+accepted only as a near-tie judged by the oracle's float64 energies (oracle/check.py); inputs
+with exact ties must give the lowest index."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle.check import check_placements
+from paper_2606_30391_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def parity(inp, label, exact=False, sel=None):
+    from paper_2606_30391_amd import festina as F
+    R = inp["requests"]["n_requests"]
+    print(f"[gpu] fronts: {label}: R={R} G={inp['gpus']['n_gpus']} W={inp['gpus']['n_waves']} "
+          f"M={inp['lut']['n_models']}", flush=True)
+    dp = F.DevicePlacement(inp, "cuda")
+    for t in (dp.choice, dp.feasible, dp.energy):
+        t.fill_(7)                                  # an unwritten entry cannot pass
+    dp.run()
+    torch.cuda.synchronize()
+    got = dp.results()
+    sel = np.arange(R) if sel is None else sel
+    ref = oracle.score_placements(inp, sel)
+    rep = check_placements(inp, sel, ref, tuple(x[sel] for x in got))
+    print(f"      {rep}", flush=True)
+    assert rep.ok, str(rep)
+    if exact:
+        assert rep.near_ties == 0 and np.array_equal(got[0][sel], ref[0]), label
+    return got
+
+
+def tiny(seed, **kw):
+    kw = dict(dict(R=400, G=40, M=2, NS=8, NF=16, W=2), **kw)
+    return W.make_tiny_placement(np.random.default_rng(seed), **kw)
+
+
+def rising_load(inp, rows=32):
+    """Decode latencies that fall with the batch row, the same at every level: a loaded GPU is
+    never dominated by a lighter one, so every distinct row stays in every cell's front."""
+    lut, g = inp["lut"], inp["gpus"]
+    r = np.arange(32, dtype=np.float32)[None, :, None, None]
+    lut["dc"][:] = 30.0 - 0.5 * r - 0.01 * np.arange(8, dtype=np.float32)[:, None]
+    g["batch"][:] = np.arange(g["n_gpus"], dtype=np.int32)[None] % rows
+    g["k_dyn_w"][:] = np.linspace(300, 500, g["n_gpus"]).astype(np.float32)
+    g["resident"][:] = 0xffffffff
+    q = inp["requests"]
+    q["slo_tbt_ms"] = np.random.default_rng(1).uniform(12.0, 32.0, q["n_requests"]).astype(np.float32)
+    return inp
+
+
+@pytest.mark.parametrize("R", [1, 15, 16, 17, 127, 128, 129, 1100])
+def test_request_chunks(R):
+    parity(W.make_placement(2, n_requests=R), f"{R} requests")
+
+
+@pytest.mark.parametrize("G,caps", [(1, False), (127, True), (128, False), (129, True), (300, True), (1030, False)])
+def test_host_chunks(G, caps):
+    """Every GPU hosts both models: one, several and partly filled chunks of 128 hosts, and more
+    GPUs than one round of the list builder."""
+    inp = tiny(11 + G, G=G, caps=caps)
+    inp["gpus"]["resident"][:] = 3
+    parity(inp, f"{G} hosts caps={caps}")
+
+
+def test_long_fronts_in_the_pool():
+    parity(rising_load(tiny(21, R=300, G=64, M=3, W=2, caps=False)), "64 steps per front")
+
+
+def test_more_long_fronts_than_the_pool_holds():
+    parity(rising_load(tiny(22, R=900, G=64, M=10, W=10, caps=False)), "100 fronts of 64 steps")
+
+
+def test_fronts_too_long_to_keep():
+    """Every cap pair and 32 loads: some cells keep more than 255 candidates."""
+    inp = rising_load(tiny(23, R=200, G=2048, M=1, W=1, caps=True))
+    parity(inp, "2048 hosts, every cap pair")
+
+
+@pytest.mark.parametrize("caps", [False, True])
+def test_every_gpu_ties(caps):
+    """All candidates of a level tie exactly, whatever order the GPUs are pruned in."""
+    inp = tiny(31, R=500, G=200, M=2, W=2, caps=caps, ties=True)
+    inp["lut"]["p0_w"] = 100.0
+    inp["gpus"]["k_dyn_w"][:] = 0.0
+    parity(inp, f"ties caps={caps}", exact=True)
+
+
+def test_equal_keys_at_several_cells_and_gpus():
+    """Two frequencies and two SM levels of equal power and latency: the least key is attained at
+    several cells; GPUs in descending load order, so the lowest id is not the lightest."""
+    inp = tiny(32, R=500, G=90, M=2, W=2, caps=True)
+    lut = inp["lut"]
+    lut["freq_level"][:] = np.repeat(lut["freq_level"][::4], 4)
+    lut["sm_level"][:] = np.repeat(lut["sm_level"][::2], 2)
+    for k in ("pf", "dc"):
+        lut[k][:] = np.repeat(np.repeat(lut[k][:, :, ::2, ::4], 2, axis=2), 4, axis=3)
+    inp["gpus"]["batch"][:] = -np.sort(-inp["gpus"]["batch"], axis=1)
+    inp["gpus"]["k_dyn_w"][:] = 350.0
+    parity(inp, "repeated cells", exact=True)
+
+
+def test_requests_scored_against_every_gpu():
+    """No prompt, no output, or a table with negative or tiny latencies, mixed with others."""
+    inp = tiny(41, R=700, M=3, caps=True)
+    q = inp["requests"]
+    q["pred_out_tokens"][::5] = 0
+    q["prompt_tokens"][::7] = 0
+    inp["lut"]["pf"][1, 3, 2, 5] = np.float32(1e-30)
+    inp["lut"]["dc"][2, 4, 1, 1] = np.float32(-3.0)
+    parity(inp, "unusual requests and tables")
+
+
+def test_slo_values():
+    """TBT SLOs different for every request of a group, and infinite, zero or NaN SLOs."""
+    inp = tiny(42, R=600, M=1, W=1, caps=True)
+    q = inp["requests"]
+    q["slo_ttft_ms"][::9] = np.inf
+    q["slo_tbt_ms"][1::9] = np.inf
+    q["slo_tbt_ms"][2::9] = 0.0
+    q["slo_tbt_ms"][3::9] = np.nan
+    q["slo_ttft_ms"][4::9] = np.nan
+    parity(inp, "SLO values")
+
+
+def test_groups_that_share_a_slot():
+    """630 buckets of shuffled requests: more groups in a chunk than sort slots keep apart."""
+    parity(tiny(51, R=5000, G=60, M=70, W=9, caps=True), "630 buckets")
+
+
+@pytest.mark.parametrize("R", [4096, 4104, 4108])
+def test_either_side_of_the_route(R):
+    """2,050 buckets: the front search takes calls of at least 4,104 requests."""
+    inp = tiny(52, R=R, G=30, M=41, W=50, caps=True)
+    parity(inp, f"2050 buckets, {R} requests", sel=np.arange(0, R, 3))

@@ -243,3 +243,31 @@ def test_wave_dispatch_waves_of_16_lanes_per_request():
     """Waves above 8,192 requests take the 16-lanes-per-request kernel."""
     inp = W.make_dispatch_waves(seed=W.DISPATCH_SEED + 400, n_requests=20000, n_gpus=256, n_waves=2)
     wave_parity(inp, inp["wave_start"], label="two waves of 10000")
+
+
+@pytest.mark.parametrize("R,G", [(1, 2048), (256, 2048), (257, 2048), (5, 2047), (3, 16385)])
+def test_few_requests_on_a_large_fleet(R, G):
+    """A block per request from 2,048 GPUs on (at most 256 requests), and host lists collected in
+    one or two rounds of 16,384 GPUs."""
+    rng = np.random.default_rng(2000 + R + G)
+    parity(W.make_tiny_dispatch(rng, R=R, G=G, M=3, NS=4, NF=6, S=4), label="large fleet")
+
+
+@pytest.mark.parametrize("S", [1, 4, 5])
+@pytest.mark.parametrize("G,R", [(60, 2049), (256, 2100), (257, 2100), (400, 300)])
+def test_wave_dispatch_group_widths(G, R, S):
+    """Either side of the rules: profiles of up to 4 steps take the batched kernel, with 16 lanes
+    per request for large waves on at most 256 GPUs; up to 400 hosts, so several batches per lane."""
+    rng = np.random.default_rng(2100 + G + S)
+    inp = W.make_tiny_dispatch(rng, R=2 * R, G=G, M=2, NS=4, NF=6, S=S)
+    inp["avail"]["resident"][:] = 3
+    wave_parity(inp, np.array([0, R, 2 * R], np.int32), label="group widths")
+
+
+def test_wave_dispatch_large_memory_demands():
+    """Requests whose memory demand exceeds 32-bit MiB, and demands of zero."""
+    rng = np.random.default_rng(2200)
+    inp = W.make_tiny_dispatch(rng, R=400, G=30, M=3, NS=3, NF=4, S=4)
+    inp["avail"]["kv_kib_per_token"][:] = [2**31 - 1, 0, 150]
+    inp["requests"]["prompt_tokens"][::7] = 2**31 - 1
+    wave_parity(inp, W.wave_bounds(400, 4), label="memory demands")

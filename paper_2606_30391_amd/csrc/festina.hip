@@ -1254,6 +1254,149 @@ __global__ void __launch_bounds__(256) k_score(PlaceArgs a) {
   score_tile_generic<CPL>(a, blockIdx.x, lds);
 }
 
+// ------------------------------------------------------------------ small calls
+// A call of few (request, GPU) pairs in one launch, where the other searches need three or four
+// that each last about as long: WPR wavefronts per request read 64 GPUs at a time (one per lane,
+// all fields together), then score the hosting ones, lanes spanning the cells, kSmallHosts of them
+// per memory round trip.  Bound by those round trips, hence several wavefronts for a larger fleet.
+//
+// FAST: 8 x 16 tables; a request whose Lout scales its prompt row exactly enough (as in the 8 x 16
+// kernel) is decided on keys, Pp * (TTFT / Lout) + Y, so that a request's result does not depend on
+// which kernel serves its call.  Every other request is decided on E = fma(Lout, Y, Pp * TTFT).
+constexpr int kSmallHosts = 4;
+constexpr int small_waves(int WPR) { return WPR > 4 ? WPR : 4; }   // wavefronts per workgroup
+
+template <int CPL, bool FAST, int WPR>
+__global__ void __launch_bounds__(small_waves(WPR) * kWave) k_small(PlaceArgs a) {
+  __shared__ float s_e[small_waves(WPR)];
+  __shared__ int s_id[small_waves(WPR)];
+  const int lane = threadIdx.x & (kWave - 1), wv = uniform(threadIdx.x >> 6);
+  const int r = blockIdx.x * (small_waves(WPR) / WPR) + wv / WPR;
+  if (WPR == 1 && r >= a.R) return;              // (several wavefronts fill a workgroup: r < R)
+  const int C = FAST ? 128 : a.C, NF = FAST ? 16 : a.NF;
+  const int m = ro(a.model)[r], w = a.wave ? ro(a.wave)[r] : 0;
+  const int pt = ro(a.prompt)[r], pr = ro(a.pred)[r];
+  const float st = ro(a.slo_ttft)[r], sb = ro(a.slo_tbt)[r];
+  float be[CPL];
+  int bg[CPL];
+#pragma unroll
+  for (int u = 0; u < CPL; ++u) {
+    be[u] = kInf;
+    bg[u] = INT_MAX;
+  }
+  const bool ok = m >= 0 && m < a.M && w >= 0 && w < a.W && pt >= 0 && pr >= 0;
+  const float lout = (float)(((long long)pr * 105 + 99) / 100);
+  bool keyed = false;
+  if (ok) {
+    const float p0 = a.p0;
+    int cj[CPL], ck[CPL];
+    bool live[CPL];
+    float f3[CPL];
+#pragma unroll
+    for (int u = 0; u < CPL; ++u) {
+      const int c = u * kWave + lane;
+      live[u] = c < C;
+      cj[u] = live[u] ? c / NF : 0;
+      ck[u] = live[u] ? c - cj[u] * NF : 0;
+      f3[u] = cube(a.freq_level[ck[u]]);
+    }
+    const float *pfm = a.pf + (size_t)m * kRows * C, *dcm = a.dc + (size_t)m * kRows * C;
+    const int prow = prompt_row(pt);
+    float rl = 1.f;
+    if (FAST && prow >= 0) {
+      bool tiny = false;
+#pragma unroll
+      for (int u = 0; u < CPL; ++u) {
+        const float v = fabsf(pfm[prow * C + u * kWave + lane]);
+        tiny = tiny || (v > 0.f && v < kTinyLatency);
+      }
+      keyed = lout >= 1.f && lout <= 0x1p40f && __ballot(tiny) == 0ull;
+      rl = keyed ? 1.f / lout : 1.f;
+    }
+    const float scale = keyed ? 1.f : lout;
+    for (int g0 = wv % WPR * kWave; g0 < a.G; g0 += WPR * kWave) {
+      const int gl = min(g0 + lane, a.G - 1);
+      const uint32_t word = a.resident[(size_t)gl * a.words + (m >> 5)];
+      const int B = a.batch[(size_t)w * a.G + gl];
+      const float kd = a.kdyn[gl];
+      const int cpv = *(a.cap_pf ? a.cap_pf + gl : &kNoCap), cdv = *(a.cap_dc ? a.cap_dc + gl : &kNoCap);
+      const int cp = a.cap_pf ? cpv : a.NS - 1, cd = a.cap_dc ? cdv : a.NS - 1;
+      const bool cand = g0 + lane < a.G && ((word >> (m & 31)) & 1u) && B >= 0 && cp >= 0 && cp < a.NS && cd >= 0 && cd < a.NS;
+      const int bb = B + 1 > kRows ? kRows : B + 1;
+      const float kapv = kd * ((float)bb * 0.03125f);
+      const int packv = (cp & 0xff) | ((cd & 0xff) << 8) | (max(bb - 1, 0) << 16);
+      unsigned long long todo = __ballot(cand);
+      while (todo) {
+        // the next hosts (the last one repeated), their table entries in one round trip
+        float tt[kSmallHosts][CPL], tb[kSmallHosts][CPL], sp[kSmallHosts][CPL], sd[kSmallHosts][CPL], kap[kSmallHosts];
+        int gh[kSmallHosts];
+#pragma unroll
+        for (int h = 0; h < kSmallHosts; ++h) {
+          const int l = __builtin_ctzll(todo);
+          if (todo & (todo - 1)) todo &= todo - 1;
+          else if (h == kSmallHosts - 1) todo = 0ull;
+          gh[h] = g0 + l;
+          kap[h] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(kapv), l));
+          const int pk = __builtin_amdgcn_readlane(packv, l);
+          const int hp = pk & 0xff, hd = (pk >> 8) & 0xff, row = pk >> 16;
+#pragma unroll
+          for (int u = 0; u < CPL; ++u) {
+            const int jp = min(cj[u], hp), jd = min(cj[u], hd);
+            tb[h][u] = dcm[row * C + jd * NF + ck[u]];
+            tt[h][u] = pfm[(prow < 0 ? row : prow) * C + jp * NF + ck[u]];
+            sp[h][u] = a.sm_level[jp];
+            sd[h][u] = a.sm_level[jd];
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < kSmallHosts; ++h)
+#pragma unroll
+          for (int u = 0; u < CPL; ++u) {
+            const float Pp = fmaf(kap[h], sp[h][u] * f3[u], p0);
+            const float Y = fmaf(kap[h], sd[h][u] * f3[u], p0) * tb[h][u];
+            const float E = keyed ? fmaf(Pp, tt[h][u] * rl, Y) : fmaf(scale, Y, Pp * tt[h][u]);
+            const bool in = live[u] && tt[h][u] < st && tb[h][u] < sb && E < be[u];
+            be[u] = in ? E : be[u];
+            bg[u] = in ? gh[h] : bg[u];
+          }
+      }
+    }
+  }
+  float e = kInf;
+  int id = INT_MAX;
+#pragma unroll
+  for (int u = 0; u < CPL; ++u) {
+    if (bg[u] != INT_MAX) {
+      const int cand = bg[u] * C + u * kWave + lane;
+      if (be[u] < e || (be[u] == e && cand < id)) {
+        e = be[u];
+        id = cand;
+      }
+    }
+  }
+  wave_argmin(e, id);
+  if (WPR > 1) {
+    if (lane == 0) {
+      s_e[wv] = e;
+      s_id[wv] = id;
+    }
+    __syncthreads();
+    for (int i = 0; i < WPR; ++i)
+      if (s_e[i] < e || (s_e[i] == e && s_id[i] < id)) {
+        e = s_e[i];
+        id = s_id[i];
+      }
+  }
+  if (lane == 0 && wv % WPR == 0) {
+    const float energy = keyed ? lout * e : e;
+    const bool found = id != INT_MAX && energy < kInf;
+    a.choice[r] = found ? id : -1;
+    a.feasible[r] = found ? 1 : 0;
+    a.energy[r] = found ? energy : kInf;
+  }
+}
+
 // ------------------------------------------------------------------ helpers of the 8 x 16 kernel
 constexpr int kXcds = 8;                         // MI355X: 8 XCDs, each with its own L2
 
@@ -2097,6 +2240,24 @@ __global__ void __launch_bounds__(256) k_migrate(MigArgs a) {
 // ------------------------------------------------------------------ host helpers
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Calls that take k_small, by how many (request, hosting GPU) pairs they score; at most 4 models
+// per GPU are taken to be resident (all of fewer models).  us per call, k_small against the front
+// search: 4,096 requests on 64 GPUs (2^17 pairs) 11.9 / 17.6, 2,048 on 128 (2^17) 16.6 / 18.5, 4,096
+// on 128 (2^18) 19.7 / 18.6, 1,024 capped on 1,024 (2^17) 19.9 / 41.8, 1 on 4,096 16.0 / 53.8; and
+// against the kernels below for 4 x 8 tables: 64 on 8 7.6 / 19.7, 16,384 on 8 (2^17) 14.8 / 25.4,
+// 16,384 on 32 (2^19) 33.0 / 39.3.
+constexpr long long kSmallPairs = 1 << 17;
+constexpr int kSmallMaxGpus = 4096;
+inline bool small_call(long long M, long long G, long long R, bool fast) {
+  const long long hosts = M <= 4 ? G : (4 * G + M - 1) / M;
+  return G <= kSmallMaxGpus && R * hosts <= (fast ? kSmallPairs : 2 * kSmallPairs);
+}
+// Wavefronts per request: enough that a wavefront has one or a few groups of 64 GPUs to read,
+// while the launch stays below the GPU's wavefront slots.
+inline int small_wpr(long long G, long long R) {
+  return G > 512 && R <= 256 ? 16 : (G > kWave && R <= 2048 ? 4 : 1);
+}
+
 struct PlaceLayout {
   size_t cnt, bstart, ntiles, tiles, gscan, host_cnt, host_list, recs, preq, key, off;
   size_t host_pos, cls_tab, pf_rowmin, pf_rowtiny, dc_min, total;
@@ -2106,6 +2267,7 @@ struct PlaceLayout {
   bool fast;                     // 8 SM x 16 frequency levels: the specialised kernel
   bool scan_local;               // k_scatter scans the bucket counts (no k_scan launch)
   size_t scatter_lds;            // dynamic LDS bytes of k_scatter
+  bool small;                    // k_small serves the call
   bool fronts;                   // the front search (fronts.hip) serves the call, with its own
   festina_fronts::Layout front;  // workspace layout
 };
@@ -2193,7 +2355,8 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
   const long long scan_ints = block_scan_ints(NB, ng, gpad > 1);
   o->scan_local = NB <= kHistMax && scan_ints <= kScanLds;
   o->scatter_lds = o->scan_local ? sizeof(int32_t) * (size_t)scan_ints : 0;
-  o->fronts = festina_fronts::layout(L, G, Q, &o->front);
+  o->small = small_call(M, Gn, R, fast);
+  o->fronts = !o->small && festina_fronts::layout(L, G, Q, &o->front);
   // (the size stays at least the other kernels', so that festina_score_placements_noalloc takes
   // and refuses the same shapes whichever search serves them)
   if (o->fronts && o->front.total > o->total) o->total = o->front.total;
@@ -2203,6 +2366,16 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
 // A caller's event recorded on the stream (the timed entry points); nullptr: nothing.
 hipError_t mark(void *ev, hipStream_t st) {
   return ev ? hipEventRecord(static_cast<hipEvent_t>(ev), st) : hipSuccess;
+}
+
+template <int CPL, bool FAST>
+void launch_small(const PlaceArgs &a, int wpr, hipStream_t st) {
+  if (wpr == 16)
+    k_small<CPL, FAST, 16><<<a.R, small_waves(16) * kWave, 0, st>>>(a);
+  else if (wpr == 4)
+    k_small<CPL, FAST, 4><<<a.R, small_waves(4) * kWave, 0, st>>>(a);
+  else
+    k_small<CPL, FAST, 1><<<(a.R + 3) / 4, small_waves(1) * kWave, 0, st>>>(a);
 }
 
 template <int CPL>
@@ -2322,6 +2495,20 @@ festina_status place_launch(const festina_lut *L, const festina_gpus *G, const f
   a.dc_min = reinterpret_cast<float *>(ws + lay.dc_min);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
+  const int cpl = C <= 64 ? 1 : (C <= 128 ? 2 : 4);
+  if (lay.small) {
+    if (mark(ev_begin, st) != hipSuccess) return FESTINA_ERR_DEVICE;
+    const int wpr = small_wpr(a.G, a.R);
+    if (lay.fast)
+      launch_small<2, true>(a, wpr, st);
+    else if (cpl == 1)
+      launch_small<1, false>(a, wpr, st);
+    else if (cpl == 2)
+      launch_small<2, false>(a, wpr, st);
+    else
+      launch_small<4, false>(a, wpr, st);
+    return hipGetLastError() == hipSuccess && mark(ev_end, st) == hipSuccess ? FESTINA_OK : FESTINA_ERR_DEVICE;
+  }
   int zb = (nb4 + 255) / 256;
   zb = zb < 1024 ? zb : 1024;
   k_init<<<zb + 9 * a.M, 256, 0, st>>>(a, zb, nb4);
@@ -2336,7 +2523,6 @@ festina_status place_launch(const festina_lut *L, const festina_gpus *G, const f
   }
   k_scatter<<<nbr, kPrepBlock, lay.scatter_lds, st>>>(a);
   if (hipGetLastError() != hipSuccess) return FESTINA_ERR_DEVICE;
-  const int cpl = C <= 64 ? 1 : (C <= 128 ? 2 : 4);
   const int wpb = lay.waves_per_block;
   size_t lds = sizeof(float) * score_lds_floats((int)C, cpl, wpb);
   if (lay.fast) {

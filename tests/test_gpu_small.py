@@ -1,0 +1,68 @@
+"""GPU parity of the one-launch placement kernel for small calls (at most 2^17 (request, GPU) pairs
+and 4,096 GPUs): at the numbers of GPUs and requests where its wavefronts per request change, for
+all table shapes, and against the other searches on the same requests."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle.check import check_placements
+from paper_2606_30391_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not torch.cuda.is_available(), reason="needs a GPU")]
+
+
+def run(inp):
+    from paper_2606_30391_amd import festina as F
+    dp = F.DevicePlacement(inp, "cuda")
+    for t in (dp.choice, dp.feasible, dp.energy):
+        t.fill_(7)                                  # an unwritten entry cannot pass
+    dp.run()
+    torch.cuda.synchronize()
+    return dp.results()
+
+
+def parity(inp, label):
+    R = inp["requests"]["n_requests"]
+    print(f"[gpu] small placement {label}: R={R} G={inp['gpus']['n_gpus']}", flush=True)
+    got = run(inp)
+    rep = check_placements(inp, np.arange(R), oracle.score_placements(inp), got)
+    print(f"      {rep}", flush=True)
+    assert rep.ok, str(rep)
+
+
+@pytest.mark.parametrize("R,G", [(1, 1), (3, 63), (5, 64), (7, 65), (2048, 63), (2048, 64), (255, 513), (256, 512),
+                                 (257, 510), (2, 1025), (31, 4096), (32, 4096), (16, 4097)])
+@pytest.mark.parametrize("caps", [False, True])
+def test_gpus_and_requests(R, G, caps):
+    rng = np.random.default_rng(R + G)
+    parity(W.make_tiny_placement(rng, R=R, G=G, M=2, NS=8, NF=16, W=2, caps=caps), f"caps={caps}")
+
+
+@pytest.mark.parametrize("NS,NF", [(1, 1), (4, 8), (5, 13), (8, 16), (3, 43), (16, 16)])
+@pytest.mark.parametrize("G", [20, 200])
+def test_table_shapes(NS, NF, G):
+    rng = np.random.default_rng(NS * 50 + NF + G)
+    parity(W.make_tiny_placement(rng, R=301, G=G, M=3, NS=NS, NF=NF, W=2, caps=True, nan_cells=True), f"{NS}x{NF}")
+
+
+@pytest.mark.parametrize("M", [4, 5, 70])
+def test_models(M):
+    rng = np.random.default_rng(70 + M)
+    parity(W.make_tiny_placement(rng, R=200, G=90, M=M, NS=8, NF=16, W=3, caps=True), f"{M} models")
+
+
+@pytest.mark.parametrize("cfg,G", [(2, 64), (3, 200), (4, 333)])
+def test_same_results_as_the_larger_call(cfg, G):
+    """A request's result does not depend on the size of the call it came with."""
+    big = W.make_placement(cfg, n_requests=40000, n_gpus=G)
+    want = run(big)
+    n = 150
+    q = big["requests"]
+    for k, v in q.items():
+        if isinstance(v, np.ndarray):
+            q[k] = np.ascontiguousarray(v[:n])
+    q["n_requests"] = n
+    for name, a, b in zip(("choice", "feasible", "energy"), want, run(big)):
+        assert np.array_equal(a[:n], b), name

@@ -2246,11 +2246,15 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // on 128 (2^18) 19.7 / 18.6, 1,024 capped on 1,024 (2^17) 19.9 / 41.8, 1 on 4,096 16.0 / 53.8; and
 // against the kernels below for 4 x 8 tables: 64 on 8 7.6 / 19.7, 16,384 on 8 (2^17) 14.8 / 25.4,
 // 16,384 on 32 (2^19) 33.0 / 39.3.
-constexpr long long kSmallPairs = 1 << 17;
+// With too few requests per (wave, model) for the front search (`sparse`) the 8 x 16 kernel's tiles of
+// 16 requests stay mostly empty, and k_small serves larger calls too: 6,007 requests in 4,200
+// buckets on 600 GPUs 35 / 104, 20,000 in 8,192 on 512 GPUs 113 / 193, 100,000 in 32,768 on 512
+// GPUs (2^22.6 pairs) 456 / 546.
+constexpr long long kSmallPairs = 1 << 17, kSparsePairs = 1 << 23;
 constexpr int kSmallMaxGpus = 4096;
-inline bool small_call(long long M, long long G, long long R, bool fast) {
+inline bool small_call(long long M, long long G, long long R, bool fast, bool sparse) {
   const long long hosts = M <= 4 ? G : (4 * G + M - 1) / M;
-  return G <= kSmallMaxGpus && R * hosts <= (fast ? kSmallPairs : 2 * kSmallPairs);
+  return G <= kSmallMaxGpus && R * hosts <= (sparse ? kSparsePairs : (fast ? kSmallPairs : 2 * kSmallPairs));
 }
 // Wavefronts per request: enough that a wavefront has one or a few groups of 64 GPUs to read,
 // while the launch stays below the GPU's wavefront slots.
@@ -2355,7 +2359,7 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
   const long long scan_ints = block_scan_ints(NB, ng, gpad > 1);
   o->scan_local = NB <= kHistMax && scan_ints <= kScanLds;
   o->scatter_lds = o->scan_local ? sizeof(int32_t) * (size_t)scan_ints : 0;
-  o->small = small_call(M, Gn, R, fast);
+  o->small = small_call(M, Gn, R, fast, fast && festina_fronts::sparse(W * M, R));
   o->fronts = !o->small && festina_fronts::layout(L, G, Q, &o->front);
   // (the size stays at least the other kernels', so that festina_score_placements_noalloc takes
   // and refuses the same shapes whichever search serves them)

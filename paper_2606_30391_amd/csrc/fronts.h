@@ -16,6 +16,9 @@ struct Layout {
   int32_t chunk;                 // requests per workgroup of the choosing kernel
 };
 
+// Too few requests per (wave, model) for fronts to pay.
+bool sparse(long long buckets, long long R);
+
 // Workspace layout when these shapes take the front search; false: they do not.
 bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests *Q, Layout *o);
 

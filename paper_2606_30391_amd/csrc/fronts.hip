@@ -920,15 +920,14 @@ hipError_t mark(void *ev, hipStream_t st) {
 
 namespace festina_fronts {
 
+// Fronts are built for every (wave, model), whether or not requests ask for it.
+bool sparse(long long buckets, long long R) { return buckets > 1024 + R / 4; }
+
 bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests *Q, Layout *o) {
   const long long M = L->n_models, Gn = G->n_gpus, W = G->n_waves, R = Q->n_requests;
   if (L->n_sm != kNS || L->n_freq != kNF || M > INT_MAX / (2 * kRows * kCells) || Gn > (1 << 24)) return false;
-  // Fronts are built for every (wave, model), 8 ns each (16 us for 2,048), whether or not
-  // requests ask for it: with few requests per bucket the search over all candidates, which only
-  // visits buckets with requests, is the cheaper one (at 2,048 buckets and 4,096 requests both
-  // take about 35 us).
   const long long buckets = W * M;
-  if (buckets > 1024 + R / 4) return false;
+  if (sparse(buckets, R)) return false;
   constexpr long long kPool = 22LL << 20;        // bytes of fronts
   const long long step = kWave * (long long)sizeof(v4f);
   const long long fit = kPool / (buckets * step);

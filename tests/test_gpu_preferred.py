@@ -163,3 +163,37 @@ def test_ewr_many_slots_per_gpu():
     rep = check_ewr(oracle.fleet_ewr(n, f, t), gpu_ewr(n, f, t))
     say(f"[gpu] EWR G={G} K={K}: {rep}")
     assert rep.ok, str(rep)
+
+
+# 16 lanes per slot: 64, 65, 128 and 129 cells are the edges of 4, 8 and 16 cells per lane;
+# 1, 15, 16 and 17 slots those of a block
+@pytest.mark.parametrize("G,K,NS,NF", [(1, 1, 4, 16), (5, 3, 5, 13), (4, 4, 8, 16), (17, 1, 3, 43)])
+def test_preferred_lanes_per_slot(G, K, NS, NF):
+    rng = np.random.default_rng(1700 + NS * NF)
+    parity_preferred(W.make_tiny_llms(rng, G=G, K=K, M=2, NS=NS, NF=NF, nan_cells=True), label="lanes per slot")
+
+
+# one block: two GPUs of a thread at once (1,024 apart), four slots per load where they are aligned
+@pytest.mark.parametrize("G,K,shift", [(1023, 4, 0), (1025, 4, 1), (2049, 8, 0), (3100, 8, 3), (2500, 5, 0)])
+def test_ewr_single_block(G, K, shift):
+    from paper_2606_30391_amd import festina as F
+    F.lib()
+    rng = np.random.default_rng(1800 + G)
+    n = rng.integers(0, K + 1, G).astype(np.int32)
+    f = rng.uniform(0.5, 1.0, (G, K)).astype(np.float32)
+    t = rng.uniform(1.0, 3000.0, (G, K)).astype(np.float32)
+    f[rng.random((G, K)) < 0.05] = np.nan
+    dev = [torch.empty(G * K + shift, dtype=torch.float32, device="cuda")[shift:] for _ in range(2)]
+    for d, h in zip(dev, (f, t)):
+        d.copy_(torch.from_numpy(h.reshape(-1)))
+    fg = torch.empty(G, dtype=torch.float32, device="cuda")
+    wg = torch.empty(G, dtype=torch.float64, device="cuda")
+    tot = torch.empty(3, dtype=torch.float64, device="cuda")
+    nb = F.festina_ewr_workspace_bytes(G)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    F.festina_fleet_ewr(G, K, torch.from_numpy(n).cuda(), dev[0], dev[1],
+                        F.festina_ewr(F._ptr(fg), F._ptr(wg), F._ptr(tot)), ws, nb)
+    torch.cuda.synchronize()
+    rep = check_ewr(oracle.fleet_ewr(n, f, t), (fg.cpu().numpy(), wg.cpu().numpy(), tot.cpu().numpy()))
+    say(f"[gpu] EWR G={G} K={K} shift={shift}: {rep}")
+    assert rep.ok, str(rep)

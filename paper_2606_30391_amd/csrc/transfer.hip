@@ -85,10 +85,18 @@ __global__ void __launch_bounds__(kCostBlock) k_transfer_costs(CostArgs a, int32
   }
 }
 
-// Fleets of at most 32 models with rows of whole 16-byte vectors: u's models are walked as
-// a wave-uniform bit loop, and per destination a model costs one bit test, a select and a
-// float64 add (byte counts are whole MiB, exact in float64); e = MiB * (2^20 * ms_per_byte),
-// the same value as bytes * ms_per_byte since scaling by 2^20 is exact.
+// Fleets of at most 32 models: u's models are walked as a wave-uniform bit loop, and per
+// destination a model costs one bit test, a select and a float64 add (byte counts are whole MiB,
+// exact in float64); e = MiB * (2^20 * ms_per_byte), the same value as bytes * ms_per_byte since
+// scaling by 2^20 is exact.
+// Bound by the stores of the matrix.  A row of a fleet that is no multiple of 4 starts at any
+// float: a thread's four entries begin at the 16-byte boundary at or below (`shift` entries
+// before the row), so all but a row's two edge vectors are stored whole; a vector's residency and
+// node words are then read at 4-byte alignment, which the load units take.
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned v4u_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 __global__ void __launch_bounds__(kCostBlock) k_transfer_costs_w1(CostArgs a, int32_t blocks_per_row) {
   const int u = blockIdx.x / blocks_per_row;
   const int part = blockIdx.x - u * blocks_per_row;
@@ -97,31 +105,51 @@ __global__ void __launch_bounds__(kCostBlock) k_transfer_costs_w1(CostArgs a, in
   const unsigned cu = __builtin_amdgcn_readfirstlane(a.resident[u]);
   const double mib_intra = a.mpb_intra * 1048576.0, mib_inter = a.mpb_inter * 1048576.0;
   float *row = a.cost + (size_t)u * a.G;
-  const int base = part * kCostBlock * 4 * kCostVecs;
+  const int shift = (int)((reinterpret_cast<uintptr_t>(row) >> 2) & 3);
+  const int base = part * kCostBlock * 4 * kCostVecs - shift;
 #pragma unroll
   for (int c = 0; c < kCostVecs; ++c) {
     const int v0 = base + (c * kCostBlock + threadIdx.x) * 4;
     if (v0 >= a.G) break;
-    const uint4 cv = *reinterpret_cast<const uint4 *>(a.resident + v0);
-    const int4 nv = *reinterpret_cast<const int4 *>(a.node + v0);
+    const bool whole = v0 >= 0 && v0 <= a.G - 4;
+    unsigned cv[4];
+    int nv[4];
+    if (whole) {
+      const v4u_a4 cw = *reinterpret_cast<const v4u_a4 *>(a.resident + v0);
+      const v4i_a4 nw = *reinterpret_cast<const v4i_a4 *>(a.node + v0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        cv[q] = cw[q];
+        nv[q] = nw[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int v = min(max(v0 + q, 0), a.G - 1);
+        cv[q] = a.resident[v];
+        nv[q] = a.node[v];
+      }
+    }
     double acc[4] = {state, state, state, state};
     for (unsigned bits = cu; bits; bits &= bits - 1) {          // u's models, wave-uniform
       const int m = __builtin_ctz(bits);
       if (m >= a.M) break;
       const double w = (double)a.weights[m];
-      acc[0] += ((cv.x >> m) & 1u) ? 0.0 : w;
-      acc[1] += ((cv.y >> m) & 1u) ? 0.0 : w;
-      acc[2] += ((cv.z >> m) & 1u) ? 0.0 : w;
-      acc[3] += ((cv.w >> m) & 1u) ? 0.0 : w;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] += ((cv[q] >> m) & 1u) ? 0.0 : w;
     }
-    const int nvv[4] = {nv.x, nv.y, nv.z, nv.w};
     float e[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      e[q] = v0 + q == u ? 0.f : (float)(acc[q] * (nvv[q] == node_u ? mib_intra : mib_inter));
-    // streaming store: the matrix is written once and not read back by this kernel
-    typedef float v4f __attribute__((ext_vector_type(4)));
-    __builtin_nontemporal_store(v4f{e[0], e[1], e[2], e[3]}, reinterpret_cast<v4f *>(row + v0));
+      e[q] = v0 + q == u ? 0.f : (float)(acc[q] * (nv[q] == node_u ? mib_intra : mib_inter));
+    if (whole) {
+      // streaming store: the matrix is written once and not read back by this kernel
+      __builtin_nontemporal_store(v4f{e[0], e[1], e[2], e[3]}, reinterpret_cast<v4f *>(row + v0));
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (v0 + q >= 0 && v0 + q < a.G) row[v0 + q] = e[q];
+    }
   }
 }
 
@@ -202,18 +230,17 @@ extern "C" festina_status festina_transfer_costs(const festina_transfer *T, floa
   a.mpb_inter = ms_per_byte(T->bw_inter_gbs);
   a.cost = cost;
   const int per_block = kCostBlock * 4 * kCostVecs;
-  const int bpr = (a.G + per_block - 1) / per_block;
-  const long long blocks = (long long)a.G * bpr;
+  // rows that start on any float (k_transfer_costs_w1) reach up to 3 entries past whole vectors
+  const bool vec = (a.G % 4 == 0) && ((reinterpret_cast<uintptr_t>(cost) & 15) == 0);
+  const bool w1 = a.words == 1;
+  const long long bpr = ((long long)a.G + (w1 && !vec ? 3 : 0) + per_block - 1) / per_block;
+  const long long blocks = a.G * bpr;
   if (blocks > INT_MAX) return FESTINA_ERR_UNSUPPORTED;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // 16-byte row stores when every row starts 16-byte aligned
-  const int vec = (a.G % 4 == 0) && ((reinterpret_cast<uintptr_t>(cost) & 15) == 0);
-  const bool aligned_in = ((reinterpret_cast<uintptr_t>(T->resident) & 15) == 0) &&
-                          ((reinterpret_cast<uintptr_t>(T->node) & 15) == 0);
-  if (vec && a.words == 1 && aligned_in)
-    k_transfer_costs_w1<<<(unsigned)blocks, kCostBlock, 0, st>>>(a, bpr);
-  else
-    k_transfer_costs<<<(unsigned)blocks, kCostBlock, 0, st>>>(a, bpr, vec);
+  if (w1)
+    k_transfer_costs_w1<<<(unsigned)blocks, kCostBlock, 0, st>>>(a, (int)bpr);
+  else                           // 16-byte row stores when every row starts 16-byte aligned
+    k_transfer_costs<<<(unsigned)blocks, kCostBlock, 0, st>>>(a, (int)bpr, vec ? 1 : 0);
   return hipGetLastError() == hipSuccess ? FESTINA_OK : FESTINA_ERR_DEVICE;
 }
 

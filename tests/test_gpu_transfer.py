@@ -80,3 +80,23 @@ def test_transfer_unaligned_cost_matrix():
     torch.cuda.synchronize()
     got = buf[1:].cpu().numpy().reshape(64, 64)
     assert np.array_equal(got, oracle.transfer_costs(inp).astype(np.float32))
+
+
+@pytest.mark.parametrize("G,M,at", [(1, 3, 3), (2, 2, 1), (6, 32, 2), (255, 9, 3), (2045, 32, 0), (2046, 5, 3), (2047, 32, 1),
+                                    (2048, 32, 2), (2051, 31, 0)])
+def test_transfer_rows_that_start_anywhere(G, M, at):
+    """Rows and a matrix on any float: every entry is the oracle's and nothing beside the matrix is written."""
+    from paper_2606_30391_amd import festina as F
+    inp = W.make_tiny_transfer(np.random.default_rng(2300 + G), G=G, M=M, NS=2, NF=2, Q=0)
+    dt = F.DeviceTransfer(inp, "cuda")
+    # residency and node words on an odd float too
+    res, node = (torch.cat([x.reshape(-1)[:1], x.reshape(-1)]) for x in (dt.t["resident"], dt.t["node"]))
+    dt.transfer.resident, dt.transfer.node = res.data_ptr() + 4, node.data_ptr() + 4
+    say(f"[gpu] transfer rows: G={G} M={M} at={at}")
+    buf = torch.full((8 + G * G + 8,), -7.0, dtype=torch.float32, device="cuda")
+    F.festina_transfer_costs(dt.transfer, buf[8 - at:])
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    end = 8 - at + G * G
+    assert np.array_equal(got[8 - at:end].reshape(G, G), oracle.transfer_costs(inp).astype(np.float32))
+    assert np.all(got[:8 - at] == -7.0) and np.all(got[end:] == -7.0)

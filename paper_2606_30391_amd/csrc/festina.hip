@@ -2090,8 +2090,9 @@ struct MigArgs {
   int32_t *best_dst;
   float *saving;
   int32_t *level;
-  v4i *drec;                     // [G][2] destination records from k_fleet:
-                                 // {hbm, SM per-mille, level mask, k_d}, {u, f[kd0]^3 * u, 0, 0}
+  v4i *drec;                     // [G] destination records from k_fleet: {hbm, SM per-mille, level
+                                 // mask, k_d}
+  float2 *duse;                  // [G] their {u, f[kd0]^3 * u}
 };
 
 // One wavefront per GPU: lane k tests frequency level k (NF <= 32) for each instance, a
@@ -2161,79 +2162,147 @@ __global__ void __launch_bounds__(256) k_fleet(MigArgs a) {
   if (lane == 0) {
     const float u = a.util[g];
     const float base = fm ? cube(a.freq_level[__builtin_ctz(fm)]) * u : 0.f;
-    a.drec[2 * g] = v4i{a.hbm[g], a.smpm[g], (int)fm, __float_as_int(a.kdyn[g])};
-    a.drec[2 * g + 1] = v4i{__float_as_int(u), __float_as_int(base), 0, 0};
+    a.drec[g] = v4i{a.hbm[g], a.smpm[g], (int)fm, __float_as_int(a.kdyn[g])};
+    a.duse[g] = make_float2(u, base);
   }
 }
 
-constexpr int kMigSrcPerBlock = 2;   // sources per block; each source's destinations in 2 halves
+constexpr int kMigSrcPerBlock = 2;   // sources per block
 
 // Best (largest saving, then lowest destination) of two candidates.
-__device__ __forceinline__ void keep_best(float &v, int &d, int &k, float ov, int od, int ok) {
-  if (ov > v || (ov == v && od < d)) {
-    v = ov;
-    d = od;
-    k = ok;
+__device__ __forceinline__ void keep_best(float &v, int &d, float ov, int od) {
+  const bool other = (ov > v) | ((ov == v) & (od < d));
+  v = other ? ov : v;
+  d = other ? od : d;
+}
+
+// keep_best with the lane that a DPP move within a row of 16 pairs this one with.
+template <int CTRL>
+__device__ __forceinline__ void keep_best_dpp(float &v, int &d) {
+  const float ov = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+  const int od = __builtin_amdgcn_update_dpp(0, d, CTRL, 0xf, 0xf, false);
+  keep_best(v, d, ov, od);
+}
+
+// A source's budgets and levels, and the best destination of this lane so far.
+struct MigSrc {
+  int remH, remU;
+  uint32_t fms;
+  float u;
+  float best;
+  int dst;
+};
+
+// cap - used, clamped to int; `fits` turns false where it is below every int (no pair fits).
+__device__ __forceinline__ int mig_room(int cap, int used, bool &fits) {
+  int room;
+  const bool over = __builtin_sub_overflow(cap, used, &room);
+  fits = fits && !(over && used > 0);
+  return over ? (used > 0 ? INT_MIN : INT_MAX) : room;
+}
+
+// Destinations d0 + lane, d0 + 64 + lane, ... (N of them, up to hi) for both sources: all records,
+// then all f_k^3, are requested before the first is used.
+template <int N, int S>
+__device__ __forceinline__ void mig_score(const MigArgs &a, int d0, int hi, int lane, int src0, float f3,
+                                          MigSrc (&s)[S]) {
+  v4i r[N];
+  float2 use[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const unsigned d = (unsigned)min(d0 + q * kWave + lane, hi - 1);
+    r[q] = a.drec[d];
+    use[q] = a.duse[d];
+  }
+  float fk[N][S];
+#pragma unroll
+  for (int q = 0; q < N; ++q)
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+      fk[q][i] = __int_as_float(__builtin_amdgcn_ds_bpermute(
+          __builtin_ctz((s[i].fms & (uint32_t)r[q].z) | 0x80000000u) << 2, __float_as_int(f3)));
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const int d = d0 + q * kWave + lane;
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      const bool ok = (d < hi) & (d != src0 + i) & (r[q].x <= s[i].remH) & (r[q].y <= s[i].remU) &
+                      ((s[i].fms & (uint32_t)r[q].z) != 0u);
+      const float added = fk[q][i] * (s[i].u + use[q].x) - use[q].y;
+      const float sv = fmaf(-__int_as_float(r[q].w), added, a.p0);
+      const bool better = ok & (sv > s[i].best);
+      s[i].best = better ? sv : s[i].best;
+      s[i].dst = better ? d : s[i].dst;
+    }
   }
 }
 
-// Four wavefronts per block: wavefront w scores source blockIdx.x * 2 + w / 2 against the
-// destinations of half w % 2, lanes spanning destinations, reading the 32-byte destination
-// records straight from the cache (the whole fleet's records, 32 B per GPU, stay in L2).  The
-// two halves' bests meet in LDS: largest saving, ties to the lowest destination.
+// Four wavefronts per block, each scoring the block's two sources against a quarter of the
+// destinations, lanes spanning destinations.  Bound by launch and the chain of round trips to
+// the cache, then by the VALU: a destination's record is read once for both sources, its two
+// parts lie densely, the pair's tests are masks without branches, and the level is found again
+// for the chosen destination only.  The lower half of a wavefront then reduces the first source
+// and the upper half the second, and the four quarters' bests meet in LDS: largest saving, ties
+// to the lowest destination.
+// 2,048 GPUs: 6.4 us (7.6 us with branches in the tests and a wavefront per source and half of
+// the destinations), the call 11.2 -> 9.8 us.  Eight records per lane cover a quarter of 2,048
+// destinations in one round trip; the last up to 384 destinations of a quarter go by twos.
+constexpr int kMigBatch = 8;
+
 __global__ void __launch_bounds__(256) k_migrate(MigArgs a) {
-  __shared__ float f3[32];
-  __shared__ float s_v[4];
-  __shared__ int s_d[4], s_k[4];
-  if (threadIdx.x < 32) f3[threadIdx.x] = threadIdx.x < a.NF ? cube(a.freq_level[threadIdx.x]) : 0.f;
-  __syncthreads();
+  constexpr int S = kMigSrcPerBlock;
+  static_assert(S == 2, "the halves of a wavefront reduce one source each");
+  __shared__ float s_v[S][4];
+  __shared__ int s_d[S][4];
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = uniform(threadIdx.x >> 6);
-  const int src = blockIdx.x * kMigSrcPerBlock + (wv >> 1);
-  const bool valid = src < a.G;
-  const int s = valid ? src : 0;
-  const long long rh = (long long)a.hbm_cap - a.hbm[s];
-  const long long ru = (long long)a.sm_cap - a.smpm[s];
-  const bool any = valid && rh >= (long long)INT_MIN && ru >= (long long)INT_MIN;
-  const int remH = (int)(rh > INT_MAX ? INT_MAX : (rh < INT_MIN ? INT_MIN : rh));
-  const int remU = (int)(ru > INT_MAX ? INT_MAX : (ru < INT_MIN ? INT_MIN : ru));
-  const v4i sx = ro(a.drec)[2 * (size_t)s], sy = ro(a.drec)[2 * (size_t)s + 1];
-  const uint32_t fms = any ? (uint32_t)sx.z : 0u;
-  const float us = __int_as_float(sy.x);
-  const int per = (a.G + 1) >> 1;
-  const int lo = (wv & 1) * per, hi = min(a.G, lo + per);
-  float bs = -kInf;
-  int bd = INT_MAX, bk = -1;
-  if (fms != 0u) {
-#pragma unroll 4
-    for (int d = lo + lane; d < hi; d += kWave) {
-      const v4i r = a.drec[2 * (size_t)d], r2 = a.drec[2 * (size_t)d + 1];
-      const uint32_t f = fms & (uint32_t)r.z;
-      const bool ok = d != src && r.x <= remH && r.y <= remU && f != 0u;
-      const int k = __builtin_ctz(f | 0x80000000u);
-      const float added = f3[k] * (us + __int_as_float(r2.x)) - __int_as_float(r2.y);
-      const float sv = fmaf(-__int_as_float(r.w), added, a.p0);
-      const bool better = ok && sv > bs;
-      bs = better ? sv : bs;
-      bd = better ? d : bd;
-      bk = better ? k : bk;
-    }
-  }
+  const float f3 = lane < a.NF ? cube(a.freq_level[lane]) : 0.f;    // lane k: f_k^3
+  const int src0 = blockIdx.x * S;
+  MigSrc s[S];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-    keep_best(bs, bd, bk, __shfl_xor(bs, off, kWave), __shfl_xor(bd, off, kWave), __shfl_xor(bk, off, kWave));
-  if (lane == 0) {
-    s_v[wv] = bs;
-    s_d[wv] = bd;
-    s_k[wv] = bk;
+  for (int i = 0; i < S; ++i) {
+    bool fits = src0 + i < a.G;
+    const int at = fits ? src0 + i : 0;
+    const v4i sx = ro(a.drec)[at];
+    s[i].remH = mig_room(a.hbm_cap, sx.x, fits);
+    s[i].remU = mig_room(a.sm_cap, sx.y, fits);
+    s[i].fms = fits ? (uint32_t)sx.z : 0u;
+    s[i].u = a.duse[at].x;
+    s[i].best = -kInf;
+    s[i].dst = INT_MAX;
+  }
+  const int per = (a.G + 3) >> 2;
+  const int hi = min(a.G, (wv + 1) * per);
+  int d0 = wv * per;
+  for (; d0 + (kMigBatch - 2) * kWave < hi; d0 += kMigBatch * kWave)
+    mig_score<kMigBatch>(a, d0, hi, lane, src0, f3, s);
+  for (; d0 < hi; d0 += 2 * kWave) mig_score<2>(a, d0, hi, lane, src0, f3, s);
+  // the lanes of half i keep source i: they send the other source's best and receive their own
+  const bool up = lane >= kWave / 2;
+  float v = up ? s[1].best : s[0].best;
+  int vd = up ? s[1].dst : s[0].dst;
+  keep_best(v, vd, __shfl_xor(up ? s[0].best : s[1].best, 32, kWave), __shfl_xor(up ? s[0].dst : s[1].dst, 32, kWave));
+  keep_best(v, vd, __shfl_xor(v, 16, kWave), __shfl_xor(vd, 16, kWave));
+  keep_best_dpp<0x140>(v, vd);               // row_mirror: lane l with 15 - l
+  keep_best_dpp<0x141>(v, vd);               // row_half_mirror: l with 7 - l
+  keep_best_dpp<0x4e>(v, vd);                // quad_perm 2, 3, 0, 1
+  keep_best_dpp<0xb1>(v, vd);                // quad_perm 1, 0, 3, 2
+  if ((lane & 31) == 0) {
+    s_v[lane >> 5][wv] = v;
+    s_d[lane >> 5][wv] = vd;
   }
   __syncthreads();
-  if ((wv & 1) == 0 && lane == 0 && valid) {
-    keep_best(bs, bd, bk, s_v[wv + 1], s_d[wv + 1], s_k[wv + 1]);
-    const bool found = bd != INT_MAX;
-    a.best_dst[src] = found ? bd : -1;
-    a.saving[src] = found ? bs : -kInf;
-    a.level[src] = found ? bk : -1;
+  const int src = src0 + (int)threadIdx.x;
+  if (threadIdx.x < S && src < a.G) {
+    const int i = threadIdx.x;
+    v = s_v[i][0];
+    vd = s_d[i][0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) keep_best(v, vd, s_v[i][w], s_d[i][w]);
+    const bool found = vd != INT_MAX;
+    a.best_dst[src] = found ? vd : -1;
+    a.saving[src] = found ? v : -kInf;
+    a.level[src] = found ? __builtin_ctz(a.drec[src].z & a.drec[vd].z) : -1;
   }
 }
 
@@ -2245,7 +2314,8 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // search: 4,096 requests on 64 GPUs (2^17 pairs) 11.9 / 17.6, 2,048 on 128 (2^17) 16.6 / 18.5, 4,096
 // on 128 (2^18) 19.7 / 18.6, 1,024 capped on 1,024 (2^17) 19.9 / 41.8, 1 on 4,096 16.0 / 53.8; and
 // against the kernels below for 4 x 8 tables: 64 on 8 7.6 / 19.7, 16,384 on 8 (2^17) 14.8 / 25.4,
-// 16,384 on 32 (2^19) 33.0 / 39.3.
+// 16,384 on 32 (2^19) 33.0 / 39.3.  (All with 2.7 us more host time per call than now: calls below
+// 8 us were the host's.)
 // With too few requests per (wave, model) for the front search (`sparse`) the 8 x 16 kernel's tiles of
 // 16 requests stay mostly empty, and k_small serves larger calls too: 6,007 requests in 4,200
 // buckets on 600 GPUs 35 / 104, 20,000 in 8,192 on 512 GPUs 113 / 193, 100,000 in 32,768 on 512
@@ -2673,6 +2743,7 @@ festina_status festina_score_migrations_timed(const festina_lut *L, const festin
   a.level = out->freq_level;
   char *ws = static_cast<char *>(workspace);
   a.drec = reinterpret_cast<v4i *>(ws);
+  a.duse = reinterpret_cast<float2 *>(ws + sizeof(v4i) * (size_t)a.G);
   hipStream_t st = static_cast<hipStream_t>(stream);
   k_fleet<<<(a.G + 3) / 4, 256, 0, st>>>(a);
   if (hipGetLastError() != hipSuccess) return FESTINA_ERR_DEVICE;

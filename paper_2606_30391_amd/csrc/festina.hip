@@ -2697,7 +2697,7 @@ static bool mig_shapes_ok(const festina_lut *L, const festina_fleet *F) {
 
 size_t festina_migrations_workspace_bytes(const festina_lut *lut, const festina_fleet *fleet) {
   if (!mig_shapes_ok(lut, fleet)) return 0;
-  return align256((size_t)32 * fleet->n_gpus);      // one 32-byte destination record per GPU
+  return align256((size_t)32 * fleet->n_gpus);      // destination records (24 bytes per GPU used)
 }
 
 festina_status festina_score_migrations_timed(const festina_lut *L, const festina_fleet *F,

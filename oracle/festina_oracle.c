@@ -755,6 +755,7 @@ static void or_dispatch_one(const or_lut *L, const or_avail *A, const or_request
         be = e;
       }
     }
+    if (bg < 0) return; /* E_min = -inf (a -inf input): no energy is within 2% of it, phase 0 */
     o->gpu = bg;
     o->freq_level = A->freq_cur[bg];
     o->sm_level = bsm;

@@ -103,3 +103,31 @@ def test_dispatch_negative_energies():
         for x, y in zip(o, b):
             assert np.array_equal(x, y)
         assert np.any(o[4][o[3] == 1] < 0)
+
+
+@pytest.mark.parametrize("where", ["k_dyn_w", "table"])
+def test_dispatch_energy_of_minus_infinity(where):
+    """A GPU whose energy is -inf (a -inf power coefficient or decode latency): no energy lies within
+    2% of E_min (the bound E_min + 0.02 |E_min| is NaN), so a request that this GPU can serve is
+    placed nowhere (phase 0); a request of another model is not touched."""
+    lut = {"n_models": 2, "n_rows": 32, "n_sm": 1, "n_freq": 1, "sm_level": W.sm_levels(1),
+           "freq_level": W.freq_levels(1), "pf": np.full((2, 32, 1, 1), 4.0, np.float32),
+           "dc": np.full((2, 32, 1, 1), 2.0, np.float32), "p0_w": 50.0}
+    avail = {"n_gpus": 3, "n_steps": 1, "freq_cur": np.zeros(3, np.int32), "batch": np.array([1, 2, 3], np.int32),
+             "k_dyn_w": np.full(3, 200.0, np.float32), "resident": np.array([[1], [3], [2]], np.uint32),
+             "t_avail_ms": np.zeros((3, 1), np.float32), "mem_free_mib": np.full((3, 1), 100, np.int32),
+             "sm_free": np.zeros((3, 1), np.int32), "kv_kib_per_token": np.ones(2, np.int32), "k_new_w": 100.0}
+    if where == "k_dyn_w":
+        avail["k_dyn_w"][0] = -np.inf
+    else:
+        lut["dc"][0, 1] = -np.inf                       # the batch row of GPU 0
+    requests = {"n_requests": 2, "model": np.array([0, 1], np.int32), "wave": None,
+                "prompt_tokens": np.full(2, 8, np.int32), "pred_out_tokens": np.full(2, 10, np.int32),
+                "slo_ttft_ms": np.full(2, 1e3, np.float32), "slo_tbt_ms": np.full(2, 1e3, np.float32)}
+    inp = {"lut": lut, "avail": avail, "requests": requests}
+    g, k, j, ph, e = oracle.dispatch(inp)
+    assert (g[0], k[0], j[0], ph[0], e[0]) == (-1, -1, -1, 0, np.inf)
+    assert ph[1] == 1 and g[1] == 1 and np.isfinite(e[1])
+    (wg, _, _, wph, _), st = oracle.dispatch_waves(inp, [0, 2])
+    assert wg.tolist() == [-1, 1] and wph.tolist() == [0, 1]
+    assert st["batch"].tolist() == [1, 3, 3]

@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(kGroup <= kWave ? kWavesPerBlock * kWave : kGr
         }
       }
       const unsigned long long wbest = group_max<kGroup>(best);
-      if (wbest != 0ull) {                 // the least-energy host is always within the bound
+      if (wbest != 0ull) {                 // the least-energy host is within the bound, unless E_min = -inf
         writer = best == wbest;            // exactly one lane of the group holds the winning key
         gsel = (int)(0xffffffu - (unsigned)(wbest & 0xffffffull));
         jsel = (int)((wbest >> 24) & 0xffull);
@@ -743,10 +743,13 @@ __global__ void __launch_bounds__(kWavesPerBlock * kWave) k_dispatch4(DspArgs a,
         for (int c = 0; c < kBatch; ++c) offer(o[c], e[c]);
       }
       const unsigned long long wbest = group_max<kGroup>(best);
-      writer = best == wbest;              // exactly one lane of the group holds the winning key
-      gsel = (int)(0xffffffu - (unsigned)(wbest & 0xffffffull));
-      jsel = (int)((wbest >> 24) & 0xffull);
-      phase = 1;
+      // (no key: E_min = -inf, of a -inf input, makes the bound NaN and no host is offered)
+      if (wbest != 0ull) {
+        writer = best == wbest;            // exactly one lane of the group holds the winning key
+        gsel = (int)(0xffffffu - (unsigned)(wbest & 0xffffffull));
+        jsel = (int)((wbest >> 24) & 0xffull);
+        phase = 1;
+      }
     } else {
       // Phase Three: the earliest available host that meets the SLOs at the top level
       int bg = INT_MAX, bsm = -1;

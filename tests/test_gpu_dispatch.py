@@ -271,3 +271,19 @@ def test_wave_dispatch_large_memory_demands():
     inp["avail"]["kv_kib_per_token"][:] = [2**31 - 1, 0, 150]
     inp["requests"]["prompt_tokens"][::7] = 2**31 - 1
     wave_parity(inp, W.wave_bounds(400, 4), label="memory demands")
+
+
+@pytest.mark.parametrize("where", ["k_dyn_w", "table", "both"])
+@pytest.mark.parametrize("G,R,S", [(40, 900, 2), (300, 2100, 4), (40, 900, 6)])
+def test_energies_of_minus_infinity(G, R, S, where):
+    """A -inf power coefficient or decode latency makes E_min -inf and the 2% bound NaN: no GPU ties
+    with it, the request is placed nowhere and commits nothing."""
+    rng = np.random.default_rng(2300 + G + S)
+    inp = W.make_tiny_dispatch(rng, R=R, G=G, M=4, NS=4, NF=6, S=S)
+    if where != "table":
+        inp["avail"]["k_dyn_w"][:3] = -np.inf
+    if where != "k_dyn_w":
+        inp["lut"]["dc"][1, ::4] = -np.inf
+    got = parity(inp, label="-inf energies")
+    assert np.any((got[3] == 0) & (inp["requests"]["model"] == 1))
+    wave_parity(inp, W.wave_bounds(R, 3), label="-inf energies")

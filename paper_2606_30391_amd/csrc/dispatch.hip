@@ -676,7 +676,7 @@ __global__ void __launch_bounds__(kWavesPerBlock * kWave) k_dispatch4(DspArgs a,
   for (int i = threadIdx.x; i < a.NS; i += blockDim.x) s_sm[i] = a.sm_level[i];
   for (int i = threadIdx.x; i < a.NF; i += blockDim.x) s_f[i] = a.freq_level[i];
   const int sub = threadIdx.x & (kGroup - 1);
-  const int r = a.r0 + (blockIdx.x * kWavesPerBlock * kWave + threadIdx.x) / kGroup;
+  const int r = a.r0 + blockIdx.x * (kWavesPerBlock * kWave / kGroup) + threadIdx.x / kGroup;
   const int rc = min(r, a.R - 1);
   const int m = a.model[rc], pt = a.prompt[rc], pd = a.pred[rc];
   const float slo_ttft = a.slo_ttft[rc], slo_tbt = a.slo_tbt[rc];
@@ -986,15 +986,16 @@ extern "C" size_t festina_dispatch_waves_workspace_bytes(const festina_lut *L, c
 // chain.  Waves of 256 / 4,096 / 32,768 requests on 1,024 GPUs (80 hosts each): 7.8 / 14.9 / 65 us
 // per wave, against 10.4 / 14.7 / 71 with 32 lanes x 4, 17.5 / 18.8 / 76 with 16 x 4 and 12.2 /
 // 25.4 / 129 with k_dispatch's loop over single hosts.  On a small fleet most of 64 lanes would
-// have no host: 4,096 requests on 128 GPUs take 10.9 us with 64 lanes, 9.9 with 16.
-constexpr int kSmallFleet = 256, kNarrowRequests = 2048;
+// have no host: 4,096 requests on 128 GPUs take 10.9 us with 64 lanes, 9.9 with 16.  A launch holds
+// fewer than 2^32 threads, so waves of 2^26 requests or more take 16 lanes whatever the fleet.
+constexpr int kSmallFleet = 256, kNarrowRequests = 2048, kWidestRequests = (1 << 26) - 1;
 static festina_status launch_dispatch4(DspArgs a, const Wave4 &w, int32_t lo, int32_t hi, hipStream_t st) {
   a.r0 = lo;
   a.R = hi;
   const long long n = (long long)hi - lo;
   constexpr int T = kWavesPerBlock * kWave;
   const auto blocks = [&](int group) { return (unsigned)((n * group + T - 1) / T); };
-  if (a.G <= kSmallFleet && n > kNarrowRequests)
+  if ((a.G <= kSmallFleet && n > kNarrowRequests) || n > kWidestRequests)
     k_dispatch4<16, 4><<<blocks(16), T, 0, st>>>(a, w);
   else
     k_dispatch4<64, 2><<<blocks(64), T, 0, st>>>(a, w);

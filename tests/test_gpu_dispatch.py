@@ -287,3 +287,28 @@ def test_energies_of_minus_infinity(G, R, S, where):
     got = parity(inp, label="-inf energies")
     assert np.any((got[3] == 0) & (inp["requests"]["model"] == 1))
     wave_parity(inp, W.wave_bounds(R, 3), label="-inf energies")
+
+
+@pytest.mark.parametrize("G", [3, 257])
+def test_wave_of_more_requests_than_64_lanes_each_can_launch(G):
+    """2^26 + 1003 requests in one wave (64 lanes each would need 2^32 threads): a pattern of 1,009
+    requests repeated, so every period of the results is the oracle's; a tenth can be placed."""
+    rng = np.random.default_rng(2400 + G)
+    P, R = 1009, 2**26 + 1003
+    inp = W.make_tiny_dispatch(rng, R=P, G=G, M=2, NS=2, NF=3, S=2)
+    q = inp["requests"]
+    q["slo_tbt_ms"][rng.random(P) < 0.9] = 0.0
+    ref, _ = oracle.dispatch_waves(inp, [0, P])
+    pattern = {k: v for k, v in q.items() if isinstance(v, np.ndarray)}
+    for k, v in pattern.items():
+        q[k] = np.tile(v, -(-R // P))[:R]
+    q["n_requests"] = R
+    say(f"[gpu] wave dispatch of {R} requests, G={G}")
+    _, st, dd = run_waves(inp, [0, R])
+    n = R // P * P
+    for k, want in zip(("gpu", "freq_level", "sm_level", "phase", "energy_mj"), ref):
+        got, want = dd.o[k], torch.from_numpy(np.ascontiguousarray(want)).cuda().to(dd.o[k].dtype)
+        assert bool((got[:n].view(-1, P) == want).all()) and bool((got[n:R] == want[:R - n]).all()), k
+    placed = (ref[3] == 1) | (ref[3] == 2)
+    per = np.bincount(ref[0][placed], minlength=G) * (R // P) + np.bincount(ref[0][:R - n][placed[:R - n]], minlength=G)
+    assert placed.any() and np.array_equal(st["batch"], inp["avail"]["batch"] + per)

@@ -162,7 +162,7 @@ static int or_candidate(const or_lut *L, const or_gpus *G, const or_requests *Q,
   if (!((G->resident[(size_t)g * words + (size_t)(m / 32)] >> (m % 32)) & 1u)) return 0;
   const int32_t B = G->batch[(size_t)w * G->n_gpus + g];
   if (B < 0) return 0;
-  const int b = (B + 1 > OR_ROWS) ? OR_ROWS : B + 1;
+  const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
   const int cp = G->cap_pf ? G->cap_pf[g] : NS - 1;
   const int cd = G->cap_dc ? G->cap_dc[g] : NS - 1;
   if (cp < 0 || cp >= NS || cd < 0 || cd >= NS) return 0;
@@ -234,7 +234,7 @@ static int or_instance_ok(const or_lut *L, const or_fleet *F, int g, int i, int 
   const int32_t B = F->inst_batch[at];
   const int prow = or_prompt_row(F->inst_prompt_tokens[at]);
   if (m < 0 || m >= L->n_models || j < 0 || j >= L->n_sm || B < 0 || prow == -2) return 0;
-  const int b = (B + 1 > OR_ROWS) ? OR_ROWS : B + 1;
+  const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
   const int row_p = prow >= 0 ? prow : b - 1;
   const float ttft = L->pf[or_cell(L, m, row_p, j, k)];
   const float tbt = L->dc[or_cell(L, m, b - 1, j, k)];
@@ -477,7 +477,7 @@ static int or_phase_best(const or_lut *L, const or_llms *Q, int g, int i, int de
   const int32_t B = Q->batch[at];
   const int prow = or_prompt_row(Q->avg_in_tokens[at]);
   if (m < 0 || m >= L->n_models || B < 0 || prow < 0 || Q->avg_out_tokens[at] < 0) return -1;
-  const int b = (B + 1 > OR_ROWS) ? OR_ROWS : B + 1;
+  const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
   const double u = (double)b / 32.0;
   const double kg = (double)Q->k_dyn_w[g];
   int best = -1;
@@ -569,7 +569,7 @@ int festina_oracle_phase_cell(const or_lut *L, const or_llms *Q, int32_t g, int3
   const int32_t B = Q->batch[at];
   const int prow = or_prompt_row(Q->avg_in_tokens[at]);
   if (m < 0 || m >= L->n_models || B < 0 || prow < 0 || Q->avg_out_tokens[at] < 0) return 0;
-  const int b = (B + 1 > OR_ROWS) ? OR_ROWS : B + 1;
+  const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
   const float lat = decode ? L->dc[or_cell(L, m, b - 1, j, k)] : L->pf[or_cell(L, m, prow, j, k)];
   const float slo = decode ? Q->slo_tbt_ms[at] : Q->slo_ttft_ms[at];
   if (!(lat < slo)) return 0;
@@ -729,7 +729,7 @@ static void or_dispatch_one(const or_lut *L, const or_avail *A, const or_request
     if (!or_avail_step(L, A, g, m, need, &ta, &sm, &mem)) continue;
     const int32_t B = A->batch[g];
     if (B < 0) continue;
-    const int b = B + 1 > OR_ROWS ? OR_ROWS : B + 1;
+    const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
     if (!or_point_ok(L, Q, r, m, prow, b, sm, A->freq_cur[g], ta, (double)A->k_dyn_w[g], &e)) continue;
     if (!any || e < emin) emin = e;
     any = 1;
@@ -745,7 +745,7 @@ static void or_dispatch_one(const or_lut *L, const or_avail *A, const or_request
       if (!or_avail_step(L, A, g, m, need, &ta, &sm, &mem)) continue;
       const int32_t B = A->batch[g];
       if (B < 0) continue;
-      const int b = B + 1 > OR_ROWS ? OR_ROWS : B + 1;
+      const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
       if (!or_point_ok(L, Q, r, m, prow, b, sm, A->freq_cur[g], ta, (double)A->k_dyn_w[g], &e)) continue;
       if (!(e <= bound)) continue;
       if (bg < 0 || mem > bmem || (mem == bmem && sm > bsm)) {
@@ -773,7 +773,7 @@ static void or_dispatch_one(const or_lut *L, const or_avail *A, const or_request
     if (!or_avail_step(L, A, g, m, need, &ta, &sm, &mem)) continue;
     const int32_t B = A->batch[g];
     if (B < 0) continue;
-    const int b = B + 1 > OR_ROWS ? OR_ROWS : B + 1;
+    const int b = B < OR_ROWS ? B + 1 : OR_ROWS;
     if (!or_point_ok(L, Q, r, m, prow, b, sm, kmax, ta, (double)A->k_dyn_w[g], &e)) continue;
     if (bg < 0 || ta < bt) {
       bg = g;
@@ -966,7 +966,7 @@ int festina_oracle_request_moves(const or_lut *L, const or_transfer *T, const or
         kv >= L->n_freq || Bu < 0 || crow < 0 || Q->remaining_tokens[q] < 0 || Q->kv_kib[q] < 0 || Q->token_kib[q] < 0)
       continue;
     decision[q] = 0;
-    const int bu = Bu + 1 > OR_ROWS ? OR_ROWS : Bu + 1;
+    const int bu = Bu < OR_ROWS ? Bu + 1 : OR_ROWS;
     const double rem = (double)Q->remaining_tokens[q] * (double)L->dc[or_cell(L, m, bu - 1, ju, ku)];
     remaining_ms[q] = rem;
     if (v == u) continue;                        /* the state stays: nothing to move */

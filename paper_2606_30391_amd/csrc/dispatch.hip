@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kListThreads) k_dsp_hosts(DspArgs a) {
         // one 64-byte record per (model, host): id, batch row + 1 (-1: no candidate),
         // current level, k; the profile's free memory, times and SM levels
         const int B = a.batch[g];
-        int4 r0 = make_int4(g, B < 0 ? -1 : (B + 1 > kRows ? kRows : B + 1), a.freq_cur[g], __float_as_int(a.kdyn[g]));
+        int4 r0 = make_int4(g, B < 0 ? -1 : min(B, kRows - 1) + 1, a.freq_cur[g], __float_as_int(a.kdyn[g]));
         int mem[4] = {0, 0, 0, 0}, tt[4] = {0, 0, 0, 0}, sm[4] = {-1, -1, -1, -1};
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -198,7 +198,7 @@ __device__ __forceinline__ Point host_point(const DspArgs &a, int g, long long n
   Point p{0, 0.0, -1, 0, 1};
   const int B = view_batch<kWaves>(a, g);
   if (B < 0) return p;
-  p.b = B + 1 > kRows ? kRows : B + 1;
+  p.b = min(B, kRows - 1) + 1;
   const size_t base = (size_t)g * a.S;
   if (a.S <= kMaxSteps) {
     int mem[kMaxSteps];
@@ -628,7 +628,7 @@ __device__ __forceinline__ void load_hosts4(const DspArgs &a, const Wave4 &w, co
       if (s < a.S && v.mem[s] >= mib) st = s;
     if (v.batch < 0 || i + c * stride >= n || !fits) st = -1;
     o[c].g = g[c];
-    o[c].b = v.batch + 1 > kRows ? kRows : v.batch + 1;
+    o[c].b = min(v.batch, kRows - 1) + 1;
     o[c].freq = v.freq;
     o[c].kd = __int_as_float(p0[c].x);
     o[c].step = st;

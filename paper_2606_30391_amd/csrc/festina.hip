@@ -574,7 +574,7 @@ __global__ void __launch_bounds__(kPrepBlock) k_prep(PlaceArgs a, int32_t nbr) {
   const int cd = a.cap_dc ? (int)cdv : a.NS - 1;
   HostRec rec;
   const bool ok = B >= 0 && cp >= 0 && cp < a.NS && cd >= 0 && cd < a.NS;
-  const int bb = B + 1 > kRows ? kRows : B + 1;
+  const int bb = min(B, kRows - 1) + 1;
   rec.row_off = ok ? (bb - 1) * a.C : -1;
   // u = b / 32 is exact; a GPU without candidates gets NaN so that every energy on it is NaN
   rec.kappa = ok ? kd * ((float)bb * 0.03125f) : kMask;
@@ -1322,7 +1322,7 @@ __global__ void __launch_bounds__(small_waves(WPR) * kWave) k_small(PlaceArgs a)
       const int cpv = *(a.cap_pf ? a.cap_pf + gl : &kNoCap), cdv = *(a.cap_dc ? a.cap_dc + gl : &kNoCap);
       const int cp = a.cap_pf ? cpv : a.NS - 1, cd = a.cap_dc ? cdv : a.NS - 1;
       const bool cand = g0 + lane < a.G && ((word >> (m & 31)) & 1u) && B >= 0 && cp >= 0 && cp < a.NS && cd >= 0 && cd < a.NS;
-      const int bb = B + 1 > kRows ? kRows : B + 1;
+      const int bb = min(B, kRows - 1) + 1;
       const float kapv = kd * ((float)bb * 0.03125f);
       const int packv = (cp & 0xff) | ((cd & 0xff) << 8) | (max(bb - 1, 0) << 16);
       unsigned long long todo = __ballot(cand);
@@ -2108,7 +2108,7 @@ __device__ __forceinline__ bool inst_ok(int m, int j, int B, int pt, const MigAr
 // Level mask of instance (m, j, B, pt) with SLOs (st, sb): lane k's test, as a ballot.
 __device__ __forceinline__ uint32_t inst_mask(const MigArgs &a, int lane, int m, int j, int B, int pt, float st,
                                               float sb) {
-  const int bb = B + 1 > kRows ? kRows : B + 1;
+  const int bb = min(B, kRows - 1) + 1;
   const int prow = pt == 0 ? bb - 1 : (min((int)(((unsigned)pt + 255u) >> 8), kRows) - 1);
   const float *pr = a.pf + (((size_t)m * kRows + prow) * a.NS + j) * a.NF;
   const float *dr = a.dc + (((size_t)m * kRows + (bb - 1)) * a.NS + j) * a.NF;

@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(kMoveBlock) k_request_moves(MoveArgs a) {
                     Bu >= 0 && ctx >= 1 && rem >= 0 && kvk >= 0 && tok >= 0;
     if (ok) {
       dec = 0;
-      const int bu = Bu + 1 > kRows ? kRows : Bu + 1;
+      const int bu = min(Bu, kRows - 1) + 1;
       const int crow = min((int)(((unsigned)ctx + 255u) >> 8), kRows) - 1;
       rem_ms = (double)rem * (double)a.dc[((size_t)m * kRows + (bu - 1)) * a.C + (size_t)ju * a.NF + ku];
       if (v != u) {

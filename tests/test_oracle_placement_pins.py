@@ -13,6 +13,7 @@ import pytest
 from hypothesis import given, settings
 from hypothesis import strategies as st
 
+import largest_batch
 import oracle
 from brute import brute_placements, padded_out as bpad, prompt_row as brow
 from conftest import golden_placement, load_golden
@@ -370,3 +371,17 @@ def test_config4_capped_levels_prefer_lower_sm_level():
     j = (ch[fe == 1] // NF) % NS
     top = np.maximum(d["gpus"]["cap_pf"][g], d["gpus"]["cap_dc"][g])
     assert np.all(j <= top)
+
+
+def test_largest_batch_reads_the_last_row():
+    """min(B + 1, 32) without overflow, in every entry point that reads a batch."""
+    def all_results(batch):
+        yield from oracle.score_placements(largest_batch.placement(batch))
+        yield from oracle.score_migrations(largest_batch.fleet(batch))
+        pref = oracle.preferred(largest_batch.llms(batch))
+        yield from (pref.values() if isinstance(pref, dict) else pref)
+        yield from oracle.dispatch(largest_batch.dispatch(batch))
+        yield from oracle.request_moves(largest_batch.transfer(batch))
+
+    for a, b in zip(all_results(31), all_results(largest_batch.INT32_MAX)):
+        assert np.array_equal(a, b, equal_nan=np.asarray(a).dtype.kind == "f")

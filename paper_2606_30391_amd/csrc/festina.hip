@@ -1260,9 +1260,10 @@ __global__ void __launch_bounds__(256) k_score(PlaceArgs a) {
 // all fields together), then score the hosting ones, lanes spanning the cells, kSmallHosts of them
 // per memory round trip.  Bound by those round trips, hence several wavefronts for a larger fleet.
 //
-// FAST: 8 x 16 tables; a request whose Lout scales its prompt row exactly enough (as in the 8 x 16
-// kernel) is decided on keys, Pp * (TTFT / Lout) + Y, so that a request's result does not depend on
-// which kernel serves its call.  Every other request is decided on E = fma(Lout, Y, Pp * TTFT).
+// FAST: 8 x 16 tables; a request whose Lout scales its prompt row exactly enough is decided on keys,
+// Pp * (TTFT / Lout) + Y, every other one on E = fma(Lout, Y, Pp * TTFT).  The front search makes the
+// same choice per request, so a result is the same from either, bit for bit.  (k_score_r16 makes it
+// per workgroup: a request whose neighbours mix TBT SLOs is decided on E there.)
 constexpr int kSmallHosts = 4;
 constexpr int small_waves(int WPR) { return WPR > 4 ? WPR : 4; }   // wavefronts per workgroup
 

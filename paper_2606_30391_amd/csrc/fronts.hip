@@ -730,8 +730,11 @@ __device__ __forceinline__ void choose_front(const FrontArgs &a, int2 info, bool
 }
 
 // The selected requests against every GPU hosting the model, four requests at a time: for
-// requests that the fronts do not serve.  Energies as E = fma(Lout, Y, Pp * TTFT); lanes are
-// cells (levels 0-3 and 4-7), each keeping its least (E, GPU).
+// requests that the fronts do not serve.  A request is decided on keys, as its bucket's front
+// would decide it, or (no prompt, Lout outside [1, 2^40], or a prompt row with tiny entries) on
+// energies E = fma(Lout, Y, Pp * TTFT): by its own fields only, so that its result does not
+// depend on whether its bucket has a front.  Lanes are cells (levels 0-3 and 4-7), each keeping
+// its least (key or E, GPU).
 __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, unsigned long long sel, int L, const Req &rq,
                                            const float *s_pd) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -744,15 +747,22 @@ __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, unsig
   sel &= L == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;   // bit L * q: request q
   while (sel) {
     int ql[4];
-    float lo[4], st[4], sb[4];
+    float lo[4], rl[4], st[4], sb[4];              // rl: 1 / Lout of a request decided on keys, else 0
     int off[4];
     for (int q = 0; q < 4; ++q) {
       ql[q] = sel ? __builtin_ctzll(sel) : -1;
       const int l = max(ql[q], 0);
       lo[q] = lane_f(rq.lout, l);
+      rl[q] = lane_f(rq.rl, l);
       st[q] = ql[q] >= 0 ? lane_f(rq.st, l) : -kInf;
       sb[q] = lane_f(rq.sb, l);
       off[q] = __builtin_amdgcn_readlane(rq.off, l);
+      if (off[q] >= 0) {
+        const float v0 = fabsf(a.pf[(unsigned)(off[q] + lane)]), v1 = fabsf(a.pf[(unsigned)(off[q] + kWave + lane)]);
+        if (__ballot((v0 > 0.f && v0 < kTinyLatency) || (v1 > 0.f && v1 < kTinyLatency)) != 0ull) rl[q] = 0.f;
+      } else {
+        rl[q] = 0.f;
+      }
       sel &= sel - 1;
     }
     float be[2][4];
@@ -788,7 +798,7 @@ __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, unsig
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             const float ttft = a.pf[(off[q] >= 0 ? (unsigned)off[q] : pfm + row) + cP];
-            const float E = fmaf(lo[q], Y, Pp * ttft);
+            const float E = rl[q] > 0.f ? fmaf(Pp, ttft * rl[q], Y) : fmaf(lo[q], Y, Pp * ttft);
             const bool ok = ttft < st[q] && tbt < sb[q] && (E < be[u][q] || (E == be[u][q] && E < kInf && g < bg[u][q]));
             be[u][q] = ok ? E : be[u][q];
             bg[u][q] = ok ? g : bg[u][q];
@@ -814,7 +824,8 @@ __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, unsig
           id = oi;
         }
       }
-      if (ql[q] >= 0 && lane == ql[q]) put_result(a, rq.r, id != INT_MAX, id, e);
+      const float energy = rl[q] > 0.f ? lo[q] * e : e;
+      if (ql[q] >= 0 && lane == ql[q]) put_result(a, rq.r, id != INT_MAX && energy < kInf, id, energy);
     }
   }
 }

@@ -78,7 +78,10 @@ def test_long_fronts_in_the_pool():
 
 
 def test_more_long_fronts_than_the_pool_holds():
-    parity(rising_load(tiny(22, R=5100, G=64, M=10, W=10, caps=False)), "100 fronts of 64 steps")
+    inp = rising_load(tiny(22, R=5100, G=64, M=10, W=10, caps=False))
+    got = parity(inp, "100 fronts of 64 steps")
+    for a, b in zip(got, parity(inp, "the same again")):   # whichever buckets got the pool's room
+        assert np.array_equal(a, b)
 
 
 def test_fronts_too_long_to_keep():

@@ -53,12 +53,10 @@ def test_models(M):
     parity(W.make_tiny_placement(rng, R=200, G=90, M=M, NS=8, NF=16, W=3, caps=True), f"{M} models")
 
 
-@pytest.mark.parametrize("cfg,G", [(2, 64), (3, 200), (4, 333)])
-def test_same_results_as_the_larger_call(cfg, G):
-    """A request's result does not depend on the size of the call it came with."""
-    big = W.make_placement(cfg, n_requests=40000, n_gpus=G)
+def same_in_a_small_call(big, n=150):
+    """Whatever serves the larger call, its first n requests have the same results in a call of
+    their own, bit for bit."""
     want = run(big)
-    n = 150
     q = big["requests"]
     for k, v in q.items():
         if isinstance(v, np.ndarray):
@@ -66,3 +64,36 @@ def test_same_results_as_the_larger_call(cfg, G):
     q["n_requests"] = n
     for name, a, b in zip(("choice", "feasible", "energy"), want, run(big)):
         assert np.array_equal(a[:n], b), name
+
+
+@pytest.mark.parametrize("cfg,G", [(2, 64), (3, 200), (4, 333)])
+def test_same_results_as_the_larger_call(cfg, G):
+    """A request's result does not depend on the size of the call it came with."""
+    same_in_a_small_call(W.make_placement(cfg, n_requests=40000, n_gpus=G))
+
+
+@pytest.mark.parametrize("entry", ["tiny prefill", "negative prefill", "negative decode", "no prompt, no output",
+                                   "long fronts"])
+def test_same_results_where_requests_have_no_front(entry):
+    """Nor on whether its (wave, model) has a front: unusual table entries and requests, and more
+    long fronts than there is room for, which the larger call serves in other ways."""
+    big = W.make_placement(4 if entry == "long fronts" else 3, n_requests=20000, n_gpus=200)
+    lut, q = big["lut"], big["requests"]
+    if entry == "tiny prefill":
+        lut["pf"][::2, 31, 7, 15] = 1e-30
+        lut["pf"][1::2, 3, 2, 5] = 1e-30
+    elif entry == "negative prefill":
+        lut["pf"][::2, 31, 7, 15] = -1.0
+        lut["pf"][1::2, 3, 2, 5] = -1.0
+    elif entry == "negative decode":
+        lut["dc"][::2, 3, 2, 5] = -1.0
+        lut["dc"][1::2, 31, 7, 15] = -1.0
+    elif entry == "no prompt, no output":
+        q["prompt_tokens"][::3] = 0
+        q["pred_out_tokens"][::4] = 0
+    else:                                           # 2,048 fronts of some 16 steps, one host each per row
+        big["gpus"]["resident"][:] = 0xffffffff
+        lut["dc"][:] = 30.0 - 0.5 * np.arange(32, dtype=np.float32)[None, :, None, None]
+        big["gpus"]["batch"][:] = np.arange(200, dtype=np.int32) % 32
+        q["slo_tbt_ms"][:] = 32.0
+    same_in_a_small_call(big)

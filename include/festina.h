@@ -41,7 +41,8 @@
  *    stream).  Outputs are valid once the caller has synchronised that stream.
  *    Calls are stateless and reentrant; concurrent calls need distinct workspaces.
  *  - Errors: a NULL required pointer, a non-positive or inconsistent size, or a
- *    workspace smaller than the matching *_workspace_bytes() value returns
+ *    workspace smaller than the matching *_workspace_bytes() value (for placements:
+ *    than the call can run in, see there) returns
  *    FESTINA_ERR_INVALID before anything is launched.  A shape the kernels do not
  *    support returns FESTINA_ERR_UNSUPPORTED before anything is launched.  A HIP
  *    launch or runtime failure returns FESTINA_ERR_DEVICE.
@@ -70,7 +71,7 @@ extern "C" {
 #define FESTINA_STATIC_PER_TASK 0    /* sweep energy: static power in every task's Power x Latency */
 #define FESTINA_STATIC_PER_BATCH 1   /* sweep energy: static power once, over the batch's longest task */
 /* Device scratch that festina_score_placements_noalloc holds per GPU (32 MiB: the
- * 262,144-request, 1,024-GPU, 64-wave placement search needs 11.3 MiB of it). */
+ * 262,144-request, 1,024-GPU, 64-wave placement search of 32 models uses all but 1 MiB of it). */
 #define FESTINA_NOALLOC_WORKSPACE_BYTES ((size_t)32 << 20)
 
 typedef enum {
@@ -145,14 +146,18 @@ typedef struct festina_placements {
   float *energy_mj;
 } festina_placements;
 
-/* Bytes of device workspace festina_score_placements needs for these shapes
- * (reads only the scalar fields).  Returns 0 for invalid shapes. */
+/* Bytes of device workspace festina_score_placements takes for these shapes at full speed
+ * (reads only the scalar fields).  Returns 0 for invalid shapes.  Searches of 8 x 16 tables
+ * may take more (up to 32 MiB) than the kernels that score every candidate need; a smaller
+ * workspace that holds those is accepted, and they serve the call.  What they need never
+ * falls as a shape grows, so a workspace of this size is enough for every call with no more
+ * models, GPUs, waves and requests. */
 size_t festina_placements_workspace_bytes(const festina_lut *lut, const festina_gpus *gpus,
                                           const festina_requests *req);
 
 /* Score all requests (Sec. 3.3 Phases One-Two; Eq. energy).  `workspace` is device
- * memory of at least festina_placements_workspace_bytes() bytes, 256-byte aligned;
- * its contents on entry do not matter and are clobbered. */
+ * memory of festina_placements_workspace_bytes() bytes (or less, see there), 256-byte
+ * aligned; its contents on entry do not matter and are clobbered. */
 festina_status festina_score_placements(const festina_lut *lut, const festina_gpus *gpus,
                                         const festina_requests *req, festina_placements *out,
                                         void *workspace, size_t workspace_bytes, void *stream);
@@ -176,8 +181,8 @@ festina_status festina_score_placements_timed(const festina_lut *lut, const fest
  * library holds on every GPU it runs on until the process ends.  The call allocates
  * nothing; the caller passes inputs and outputs as for festina_score_placements, and gets
  * the same outputs.  The array's address on the current device is looked up on the first
- * call made with that device current.  Shapes whose festina_placements_workspace_bytes()
- * exceeds FESTINA_NOALLOC_WORKSPACE_BYTES return FESTINA_ERR_TOO_LARGE before anything is
+ * call made with that device current.  Shapes that festina_score_placements would not
+ * accept with FESTINA_NOALLOC_WORKSPACE_BYTES return FESTINA_ERR_TOO_LARGE before anything is
  * launched.  Every call on one GPU shares that GPU's array: calls that overlap in time on
  * one GPU (on different streams or from different host threads) race and their results
  * are undefined; calls ordered on one stream are safe, since each call clears what it

@@ -2336,6 +2336,7 @@ inline int small_wpr(long long G, long long R) {
 struct PlaceLayout {
   size_t cnt, bstart, ntiles, tiles, gscan, host_cnt, host_list, recs, preq, key, off;
   size_t host_pos, cls_tab, pf_rowmin, pf_rowtiny, dc_min, total;
+  size_t ceiling;                // the most that total is for any shape with no dimension larger
   int32_t NB, tile, max_tiles, waves_per_block, nch, gpad;
   int32_t gw, ng;                // buckets per group and groups
   int32_t split;                 // 8 x 16 kernel: wavefronts per tile (1, 2 or 4)
@@ -2343,8 +2344,10 @@ struct PlaceLayout {
   bool scan_local;               // k_scatter scans the bucket counts (no k_scan launch)
   size_t scatter_lds;            // dynamic LDS bytes of k_scatter
   bool small;                    // k_small serves the call
-  bool fronts;                   // the front search (fronts.hip) serves the call, with its own
-  festina_fronts::Layout front;  // workspace layout
+  bool fronts;                   // the front search (fronts.hip) serves the call, where it has
+  festina_fronts::Layout front;  // front.total bytes of workspace (its own layout)
+  // workspace bytes of a call at full speed; total bytes are enough (the kernels below serve it)
+  size_t full() const { return fronts && front.total > ceiling ? front.total : ceiling; }
 };
 
 bool place_shapes_ok(const festina_lut *L, const festina_gpus *G, const festina_requests *Q) {
@@ -2393,30 +2396,38 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
   const int gpad = fast ? wpb / split : 1;
   const long long max_tiles = (R + tile - 1) / tile + NB + (long long)(gpad - 1) * ng;
   if (max_tiles > INT_MAX - 8) return false;   // the grid is rounded up to a multiple of 8
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = off;
-    off = align256(off + bytes);
-    return at;
-  };
-  o->cnt = take(sizeof(int32_t) * ((NB + 3) & ~3LL));       // counters
-  o->bstart = take(sizeof(int32_t) * (NB + 1));
-  o->ntiles = take(sizeof(int32_t));
-  o->tiles = take(sizeof(int2) * max_tiles);
-  o->gscan = take(sizeof(int32_t) * (gpad > 1 ? 2 * (ng + 1) : 1));
-  o->host_cnt = take(sizeof(int32_t) * M);
-  o->host_list = take(sizeof(int32_t) * M * Gn);
-  o->recs = take(sizeof(HostRec) * W * Gn);
-  o->preq = take(sizeof(ReqRec) * (R > 0 ? R : 1));
-  o->key = take(sizeof(int32_t) * (R > 0 ? R : 1));
-  o->off = take(sizeof(int32_t) * (R > 0 ? R : 1));
   const long long nch = fast ? (Gn + kHcap - 1) / kHcap : 0;
-  o->host_pos = take(sizeof(int32_t) * (fast ? M * Gn : 1));
-  o->cls_tab = take(sizeof(int32_t) * (fast ? M * nch * (kClasses + 1) : 1));
-  o->pf_rowmin = take(sizeof(float) * M * kRows);
-  o->pf_rowtiny = take(sizeof(float) * M * kRows);
-  o->dc_min = take(sizeof(float) * M);
-  o->total = off;
+  const auto laid_out = [&](long long tiles, long long scan) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = off;
+      off = align256(off + bytes);
+      return at;
+    };
+    o->cnt = take(sizeof(int32_t) * ((NB + 3) & ~3LL));       // counters
+    o->bstart = take(sizeof(int32_t) * (NB + 1));
+    o->ntiles = take(sizeof(int32_t));
+    o->tiles = take(sizeof(int2) * tiles);
+    o->gscan = take(sizeof(int32_t) * scan);
+    o->host_cnt = take(sizeof(int32_t) * M);
+    o->host_list = take(sizeof(int32_t) * M * Gn);
+    o->recs = take(sizeof(HostRec) * W * Gn);
+    o->preq = take(sizeof(ReqRec) * (R > 0 ? R : 1));
+    o->key = take(sizeof(int32_t) * (R > 0 ? R : 1));
+    o->off = take(sizeof(int32_t) * (R > 0 ? R : 1));
+    o->host_pos = take(sizeof(int32_t) * (fast ? M * Gn : 1));
+    o->cls_tab = take(sizeof(int32_t) * (fast ? M * nch * (kClasses + 1) : 1));
+    o->pf_rowmin = take(sizeof(float) * M * kRows);
+    o->pf_rowtiny = take(sizeof(float) * M * kRows);
+    o->dc_min = take(sizeof(float) * M);
+    return off;
+  };
+  // the most tiles and groups of a shape up to this one (a smaller one may have more: its tiles are
+  // smaller, its groups padded further, its waves in more slabs)
+  const long long small_tiles = R < 4096LL * kQ ? (R + kQ - 1) / kQ : 4096;
+  o->ceiling = fast ? laid_out((R + tile - 1) / tile + NB + (wpb - 1) * 2LL * M * kXcds, 2 * (2LL * M * kXcds + 1))
+                    : laid_out((R + tile - 1) / tile > small_tiles ? max_tiles : small_tiles + NB, 1);
+  o->total = laid_out(max_tiles, gpad > 1 ? 2 * (ng + 1) : 1);
   o->nch = (int32_t)nch;
   o->NB = (int32_t)NB;
   o->gw = (int32_t)gw;
@@ -2432,9 +2443,6 @@ bool place_layout(const festina_lut *L, const festina_gpus *G, const festina_req
   o->scatter_lds = o->scan_local ? sizeof(int32_t) * (size_t)scan_ints : 0;
   o->small = small_call(M, Gn, R, fast, fast && festina_fronts::sparse(W * M, R));
   o->fronts = !o->small && festina_fronts::layout(L, G, Q, &o->front);
-  // (the size stays at least the other kernels', so that festina_score_placements_noalloc takes
-  // and refuses the same shapes whichever search serves them)
-  if (o->fronts && o->front.total > o->total) o->total = o->front.total;
   return true;
 }
 
@@ -2482,7 +2490,7 @@ size_t festina_placements_workspace_bytes(const festina_lut *lut, const festina_
                                           const festina_requests *req) {
   PlaceLayout lay;
   if (!place_layout(lut, gpus, req, &lay)) return 0;
-  return lay.total;
+  return lay.full();
 }
 
 }  // extern "C"
@@ -2506,7 +2514,8 @@ festina_status place_args(const festina_lut *L, const festina_gpus *G, const fes
   return FESTINA_OK;
 }
 
-// The launches of one placement call on a checked workspace of lay.total bytes; ev_begin /
+// The launches of one placement call on a checked workspace of lay.total bytes (lay.front.total with
+// lay.fronts); ev_begin /
 // ev_end (the timed entry point, else nullptr) are recorded around the scoring kernel.
 festina_status place_launch(const festina_lut *L, const festina_gpus *G, const festina_requests *Q,
                             const festina_placements *out, const PlaceLayout &lay, char *ws, void *stream,
@@ -2667,6 +2676,8 @@ festina_status festina_score_placements_timed(const festina_lut *L, const festin
   if (s != FESTINA_OK || Q->n_requests == 0) return s;
   if (!workspace || workspace_bytes < lay.total || (((uintptr_t)workspace) & 255) != 0)
     return FESTINA_ERR_INVALID;
+  // a workspace sized for a call without fronts (more waves, or the other kernels alone)
+  if (lay.fronts && workspace_bytes < lay.front.total) lay.fronts = false;
   return place_launch(L, G, Q, out, lay, static_cast<char *>(workspace), stream, score_begin, score_end);
 }
 
@@ -2682,7 +2693,7 @@ festina_status festina_score_placements_noalloc(const festina_lut *L, const fest
   PlaceLayout lay;
   const festina_status s = place_args(L, G, Q, out, &lay);
   if (s != FESTINA_OK || Q->n_requests == 0) return s;
-  if (lay.total > kScratchBytes) return FESTINA_ERR_TOO_LARGE;
+  if (lay.total > kScratchBytes) return FESTINA_ERR_TOO_LARGE;   // (fronts are laid out within it)
   char *ws = scratch_for_current_device();
   if (!ws) return FESTINA_ERR_DEVICE;
   return place_launch(L, G, Q, out, lay, ws, stream);

@@ -74,6 +74,26 @@ def test_placement_workspace_grows_with_shapes(lib):
     assert F.festina_placements_workspace_bytes(lut, gpus, req) == 0
 
 
+@no_gpu
+@pytest.mark.parametrize("more,fewer", [
+    (dict(M=32, G=1024, W=128, R=262144), dict(M=32, G=1024, W=64, R=262144)),    # no fronts with 4,096 buckets
+    (dict(M=32, G=333, W=64, R=20011), dict(M=32, G=333, W=64, R=3000)),          # nor for few requests each
+    (dict(M=32, G=333, W=64, R=3000), dict(M=32, G=333, W=8, R=3000)),
+    (dict(M=32, G=400000, W=1, R=65536), dict(M=32, G=1000, W=1, R=65536)),       # nor past the scratch size
+    (dict(M=262, G=89, W=263, R=147526), dict(M=262, G=89, W=262, R=147526)),     # other kernels' padding
+])
+def test_a_placement_workspace_serves_every_smaller_shape(lib, more, fewer):
+    """A caller that sizes its workspace once, for its largest call, is not refused a smaller one."""
+    def call(nbytes, **shape):
+        lut, gpus, req, out = _structs(NS=8, NF=16, **shape)
+        return _call(lut, gpus, req, out, C.c_void_p(0x1000), nbytes)
+
+    nbytes = F.festina_placements_workspace_bytes(*_structs(NS=8, NF=16, **more)[:3])
+    for shape in (more, fewer):                     # accepted, and nothing to launch on
+        assert call(nbytes, **shape) == F.FESTINA_ERR_DEVICE
+        assert call(1 << 12, **shape) == F.FESTINA_ERR_INVALID
+
+
 def _call(lut, gpus, req, out, ws, nbytes):
     return lib_().festina_score_placements(C.byref(lut), C.byref(gpus), C.byref(req), C.byref(out),
                                            ws, nbytes, None)

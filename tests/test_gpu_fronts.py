@@ -146,3 +146,22 @@ def test_either_side_of_the_route(R):
     """2,050 buckets: the front search takes calls of at least 4,104 requests."""
     inp = tiny(52, R=R, G=1400, M=41, W=50, caps=True)
     parity(inp, f"2050 buckets, {R} requests", sel=np.arange(0, R, 6))
+
+
+def test_a_workspace_without_room_for_fronts():
+    """A workspace sized for a call of more waves, which has no fronts, is less than the fronts of
+    fewer waves take: the kernels that score every candidate serve the call."""
+    from paper_2606_30391_amd import festina as F
+    inp = tiny(61, R=13000, G=100, M=32, W=64, caps=True)
+    dp = F.DevicePlacement(inp, "cuda")
+    more = F.festina_gpus(100, 128, *([None] * 5))
+    nbytes = F.festina_placements_workspace_bytes(dp.lut, more, dp.req)
+    assert nbytes < dp.ws_bytes
+    print(f"[gpu] fronts: workspace of {nbytes} bytes instead of {dp.ws_bytes}", flush=True)
+    dp.workspace = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    dp.ws_bytes = nbytes
+    dp.run()
+    torch.cuda.synchronize()
+    sel = np.arange(0, 13000, 9)
+    rep = check_placements(inp, sel, oracle.score_placements(inp, sel), tuple(x[sel] for x in dp.results()))
+    assert rep.ok, str(rep)

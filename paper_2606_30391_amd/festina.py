@@ -234,9 +234,13 @@ def _ptr(t):
 def _stream_handle(stream):
     if stream is None:
         # the handle of torch.cuda.current_stream() without its Stream object: that object took
-        # 3.0 us of the 7 us a one-launch call keeps the host, this 0.3 us
+        # 3.0 us of the 7 us a one-launch call keeps the host, this 0.3 us (the name is torch's own,
+        # so a torch without it takes the public way)
         import torch
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return C.c_void_p(raw(torch.cuda.current_device()))
     if isinstance(stream, int):
         return C.c_void_p(stream)
     return C.c_void_p(stream.cuda_stream)

@@ -436,3 +436,13 @@ def test_noalloc_placement_rejects_bad_arguments_and_oversized_inputs(lib):
     assert L.festina_score_placements_noalloc(None, C.byref(gpus), C.byref(req), C.byref(out), None) == \
         F.FESTINA_ERR_INVALID
     assert call(*_structs(R=0)) == F.FESTINA_OK                           # nothing to do
+
+
+def test_stream_handle_without_torchs_private_name(monkeypatch):
+    """The current stream's handle comes from the public Stream object where torch has no raw accessor."""
+    import types
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert F._stream_handle(None).value == 0x1230
+    assert F._stream_handle(0x1240).value == 0x1240

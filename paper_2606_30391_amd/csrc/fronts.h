@@ -10,7 +10,7 @@
 namespace festina_fronts {
 
 struct Layout {
-  size_t host_cnt, hosts, rowle, model_flags, row_max, info, pool_used, front, total;
+  size_t host_cnt, hosts, rowle, dc_positive, row_max, info, pool_used, front, total;
   int32_t buckets;               // n_waves * n_models
   int32_t cap, pool_steps;       // front steps per bucket (both SM-level ranges), and in the pool
   int32_t chunk;                 // requests per workgroup of the choosing kernel

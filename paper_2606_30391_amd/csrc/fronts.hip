@@ -29,14 +29,16 @@
 // dropped candidate's key is never below its dominator's.  Equal keys go to the lowest index:
 // a candidate is dropped in favour of a higher-indexed one only where its key is strictly
 // larger after rounding (margins in both Pp and Y).  Requests without a prompt, with a padded
-// output outside [1, 2^40], or that read table rows with negative or tiny values, and buckets
-// whose front does not fit, are scored against every hosting GPU instead (choose_all).
+// output outside [1, 2^40], or whose prompt row holds negative or tiny entries, and buckets whose
+// front does not fit, are scored against every hosting GPU instead (choose_all).  A negative decode
+// latency only keeps its hosts from the comparison of whole hosts (it turns the order of their Y).
 #include "fronts.h"
 
 #include <hip/hip_runtime.h>
 
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -61,14 +63,19 @@ constexpr float kTinyLatency = 0x1p-86f;
 // roundings of the exact terms when the GPUs' power coefficients are compared (kGapHost).
 constexpr float kGapCell = 0x1p-21f;
 constexpr float kGapHost = 0x1p-19f;
+// Power factors s_j f_k^3 and power coefficients up to this size cannot make a power infinite.
+constexpr float kMaxFactor = 0x1p60f;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 
-// model_flags: the decode table holds a negative entry / only entries large enough for the
-// host-level margin (or never feasible)
-constexpr int kDcNegative = 1, kDcPositive = 2;
+// row_max of a prefill row with a negative entry, and of one with a tiny entry
+constexpr float kRowNegative = -1.f, kRowTiny = -2.f;
+constexpr int kOddRows = 1 << 24;                // in a bucket's info: its model has such rows
+// How k_choose decides a request: by its bucket's front, or against every hosting GPU: without a
+// prompt, on energies (Lout or its prompt row do not allow keys), or on keys (negative prompt row).
+enum Kind { kByFront = 0, kNoPrompt = 1, kByEnergy = 2, kByKey = 3 };
 
 struct FrontArgs {
   int32_t M, G, W, words, R, cap, chunk, n_chunks;
@@ -87,11 +94,14 @@ struct FrontArgs {
   int32_t *host_cnt;             // [M]
   int2 *hosts;                   // [M][G] {GPU, cap_pf | cap_dc << 3 | first << 6 | end << 14}: the
                                  // host's class segment [first, end) within its chunk
-  uint32_t *rowle;               // [M][32] bit b of word a: row a's decode latencies <= row b's
-  int32_t *model_flags;          // [M]
-  float *row_max;                // [M][32] largest finite prefill entry of the row; -1: the row
-                                 // holds a negative or tiny entry
-  int2 *info;                    // [W * M] {nA | nB << 8 | span << 16, first step}, or {-1, }: no front
+  uint32_t *rowle;               // [M][32] bit b of word a: row a's decode latencies <= row b's (0: row
+                                 // a holds a negative entry)
+  int32_t *dc_positive;          // [M] whether every decode entry is large enough for the host-level
+                                 // margin (or never feasible)
+  float *row_max;                // [M][32] largest finite prefill entry of the row, or kRowNegative,
+                                 // kRowTiny
+  int2 *info;                    // [W * M] {nA | nB << 8 | span << 16 | kOddRows, first step}, or
+                                 // {-1, }: no front
   v4f *front;                    // steps of 64 {Pp, Y, TBT, id = GPU * 8 + SM level}: `cap` per bucket,
                                  // then a pool for longer fronts; in a bucket's span the nA steps of
                                  // range A (SM levels 0-3) from the start, nB of range B from the end
@@ -197,11 +207,13 @@ __device__ __forceinline__ void model_rows(const FrontArgs &a, int m, int part) 
       add_all(__ballot((v0 <= t0[b]) & (v1 <= t1[b])), 1u << b, bits);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (lane == 0) a.rowle[m * kRows + x0 + i] = bits;
+    // a row with a negative entry takes no part in the comparison of hosts: not even itself is above it
+    const bool neg = __ballot((u0[i] < 0.f) | (u1[i] < 0.f)) != 0ull;
+    if (lane == 0) a.rowle[m * kRows + x0 + i] = neg ? 0u : bits;
   }
   if (x0 == 0) {
-    const bool neg = __ballot(mn < 0.f) != 0ull, small = __ballot(mn < 0x1p-60f) != 0ull;
-    if (lane == 0) a.model_flags[m] = (neg ? kDcNegative : 0) | (small ? 0 : kDcPositive);
+    const bool small = __ballot(mn < 0x1p-60f) != 0ull;
+    if (lane == 0) a.dc_positive[m] = small ? 0 : 1;
   }
 }
 
@@ -214,12 +226,12 @@ __global__ void __launch_bounds__(kModelBlock) k_models(FrontArgs a) {
     const float *p = a.pf + (size_t)row * kCells;
     const float v0 = p[lane], v1 = p[64 + lane];
     const float a0 = fabsf(v0), a1 = fabsf(v1);
-    const bool odd = v0 < 0.f || v1 < 0.f || (a0 > 0.f && a0 < kTinyLatency) || (a1 > 0.f && a1 < kTinyLatency);
+    const bool neg = __ballot(v0 < 0.f || v1 < 0.f) != 0ull;
+    const bool tiny = __ballot((a0 > 0.f && a0 < kTinyLatency) || (a1 > 0.f && a1 < kTinyLatency)) != 0ull;
     float mx = fmaxf(v0 < kInf ? v0 : 0.f, v1 < kInf ? v1 : 0.f);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
-    const bool any = __ballot(odd) != 0ull;
-    if (lane == 0) a.row_max[row] = any ? -1.f : mx;
+    if (lane == 0) a.row_max[row] = tiny ? kRowTiny : (neg ? kRowNegative : mx);
     return;
   }
   if ((int)blockIdx.x >= a.M) {
@@ -291,6 +303,8 @@ __global__ void __launch_bounds__(kModelBlock) k_models(FrontArgs a) {
 }
 
 // ------------------------------------------------------------------ per (wave, model)
+constexpr int kNegativeHost = 64;                // beside a host's caps: its powers or latencies may be
+                                                 // negative
 constexpr int kFrontBlock = 128;                 // one wavefront per range of SM levels
 static_assert(kFrontBlock == kChunkHosts && kFrontBlock == kCells, "one thread per chunk host and per cell");
 
@@ -308,7 +322,7 @@ __device__ __forceinline__ bool dominates(const Line &h, float y, float t, int i
 
 __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   __shared__ v4i s_h[kChunkHosts];               // {kappa, GPU, row, rowle word} of the chunk's hosts
-  __shared__ v4i s_s[kChunkHosts];               // undominated hosts {kappa, GPU, row, caps}, then
+  __shared__ v4i s_s[kChunkHosts];               // undominated hosts {kappa, GPU, row, caps | kNegativeHost}, then
   __shared__ v4i s_o[kChunkHosts];               // by ascending kappa
   __shared__ float s_row[kStage][kCells];        // their decode rows
   __shared__ float s_pd[kCells];                 // s_j * f_k^3
@@ -319,7 +333,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   const int w = bucket / a.M, m = bucket - w * a.M;
   const int t = threadIdx.x, lane = t & (kWave - 1), r = uniform(t >> 6);
   const int n = ro(a.host_cnt)[m];
-  const int flags = ro(a.model_flags)[m];
+  const int positive = ro(a.dc_positive)[m];
   const float p0 = a.p0;
   const float pd = a.sm_level[t >> 4] * cube(a.freq_level[t & 15]);
   if (t < kRows) s_rl[t] = a.rowle[m * kRows + t];
@@ -328,7 +342,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
     float mn = pd;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) mn = fminf(mn, __shfl_xor(mn, off, kWave));
-    const bool odd = __ballot(!(pd >= 0.f && pd < kInf)) != 0ull;
+    const bool odd = __ballot(!(pd >= 0.f && pd <= kMaxFactor)) != 0ull;
     if (lane == 0) {
       s_pmin[r] = mn;
       s_bad[r] = odd;
@@ -336,17 +350,14 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   }
   __syncthreads();
   const float pmin = fminf(s_pmin[0], s_pmin[1]);
-  bool bad = s_bad[0] || s_bad[1] || !(p0 >= 0.f && p0 < kInf) || (flags & kDcNegative);
-  const bool margin = p0 >= 0x1p-20f && (flags & kDcPositive);
-  // the largest request term of this model (1 / Lout <= 1), and its rows' flags
-  float xmax;
-  {
-    const float v = a.row_max[m * kRows + (lane & (kRows - 1))];
-    bad = bad || __ballot(v < 0.f) != 0ull;
-    xmax = v;
+  bool bad = s_bad[0] || s_bad[1] || !(p0 >= 0.f && p0 < kInf);
+  const bool margin = p0 >= 0x1p-20f && positive != 0;
+  // the largest request term of the rows that the front serves (1 / Lout <= 1)
+  float xmax = a.row_max[m * kRows + (lane & (kRows - 1))];
+  const bool odd_rows = __ballot(xmax < 0.f) != 0ull;
+  xmax = fmaxf(xmax, 0.f);
 #pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) xmax = fmaxf(xmax, __shfl_xor(xmax, off, kWave));
-  }
+  for (int off = 16; off >= 1; off >>= 1) xmax = fmaxf(xmax, __shfl_xor(xmax, off, kWave));
 
   v4f *front = a.front + (size_t)bucket * a.cap * kWave;
   int first = bucket * a.cap, span = a.cap;
@@ -361,12 +372,13 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   int cnt = 0;
   // one candidate of this lane's cell (where `on`), of Pp at least hp, read at byte offset at
   // of its host's decode row; kp is the host's kappa
-  const auto consider = [&](bool on, float kp, float Pp, const float *row, unsigned at, int id) {
+  const auto consider = [&](bool on, float kp, float Pp, const float *row, unsigned at, int id, float xm) {
     const float tb = row[at], y = fmaf(kp, s_pd[at], p0) * tb;
     // a Y this far below y leaves a strictly smaller key after the one rounding of the FMA,
     // whatever the request: keys are at most Pp * xmax + Y.  (An infinite or NaN TBT makes Y
-    // infinite or NaN.)
-    const float strict = fmaf(-kGapCell, fmaf(Pp, xmax, y), y);
+    // infinite or NaN.  xm is xmax, or NaN where the host's powers or latencies may be negative:
+    // so is strict then, and nothing compares below it.)
+    const float strict = fmaf(-kGapCell, fmaf(Pp, xm, y), y);
     if (on & (y < kInf) & !dominates(h1, y, tb, id, strict) & !dominates(h2, y, tb, id, strict)) {
       if (cnt < span) front[(unsigned)((r == 0 ? cnt : span - 1 - cnt) * kWave + lane)] = v4f{Pp, y, tb, __int_as_float(id)};
       ++cnt;
@@ -390,12 +402,13 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
       row = max(bb - 1, 0);
       kap = B >= 0 ? kd * ((float)bb * 0.03125f) : kMask;   // NaN: no candidate
     }
-    bad = bad || kap < 0.f;
-    s_h[t] = v4i{__float_as_int(kap), g, row, (int)s_rl[row]};
+    bad = bad || kap < -kMaxFactor;
+    const uint32_t rl = kap >= 0.f ? s_rl[row] : 0u;   // (negative powers turn the order of Y, too)
+    s_h[t] = v4i{__float_as_int(kap), g, row, (int)rl};
     __syncthreads();
     // dropped where one host of its class is no worse on every cell
     bool keep = kap == kap;
-    if (t < nc) {
+    if (t < nc && rl != 0u) {
       const int lo = (pack >> 6) & 0xff, hi = (pack >> 14) & 0xff;
       const float gap = kGapHost * fmaf(kap, pmin, p0);
 #pragma unroll 4
@@ -411,7 +424,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
     if (lane == 0) s_n[r] = __popcll(bal);
     __syncthreads();
     const int ns = s_n[0] + s_n[1];
-    const v4i mine = v4i{__float_as_int(kap), g, row, pack & 63};
+    const v4i mine = v4i{__float_as_int(kap), g, row, (pack & 63) | (rl == 0u ? kNegativeHost : 0)};
     if (keep) s_s[(r ? s_n[0] : 0) + __popcll(bal & ((1ull << lane) - 1ull))] = mine;
     __syncthreads();
     if (t < ns) {
@@ -448,16 +461,17 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
       for (int i = 0; i < nb; ++i) {
         const v4i o = next;
         next = s_o[min(s0 + i + 1, ns - 1)];
-        const int caps = uniform(o.w), cp = caps & 7, cd = caps >> 3;
+        const int caps = uniform(o.w), cp = caps & 7, cd = (caps >> 3) & 7;
         if (cp < r * 4) continue;                // no cell of this range
+        const float xm = caps & kNegativeHost ? kMask : xmax;
         const float kp = uniformf(__int_as_float(o.x));
         const int gid = uniform(o.y) * kNS;
         const float Pp = fmaf(kp, pdp, p0);
         // the prefill-capped candidates (decode levels above cp, the highest first: lower TBT
         // first gives shorter fronts), then the GPU's own level
         if ((cp >> 2) == r)
-          for (int jx = cd; jx > cp; --jx) consider((jp == cp) & (Pp < kInf), kp, Pp, s_row[i], jx * 16 + k, gid + jx);
-        consider((jp <= cp) & (Pp < kInf), kp, Pp, s_row[i], min(jp, cd) * 16 + k, gid + jp);
+          for (int jx = cd; jx > cp; --jx) consider((jp == cp) & (Pp < kInf), kp, Pp, s_row[i], jx * 16 + k, gid + jx, xm);
+        consider((jp <= cp) & (Pp < kInf), kp, Pp, s_row[i], min(jp, cd) * 16 + k, gid + jp, xm);
       }
       __syncthreads();
     }
@@ -490,7 +504,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   front = a.front + (size_t)first * kWave;
   __syncthreads();                               // s_n is rewritten
   }
-  if (t == 0) a.info[bucket] = bad ? make_int2(-1, 0) : make_int2(s_cnt[0] | (s_cnt[1] << 8) | (span << 16), first);
+  if (t == 0) a.info[bucket] = bad ? make_int2(-1, 0) : make_int2(s_cnt[0] | (s_cnt[1] << 8) | (span << 16) | (odd_rows ? kOddRows : 0), first);
 }
 
 // ------------------------------------------------------------------ choosing
@@ -540,9 +554,12 @@ __device__ __forceinline__ float wave_min(const float (&v)[N]) {
 #pragma unroll
     for (int p = 0; p < 2; ++p) c[p] = vmin(b3 ? w[p + 2] : w[p], dppf<kDppRor8>(b3 ? w[p] : w[p + 2]));
     d = vmin(b2 ? c[1] : c[0], dppf<kDppHalfMirror>(b2 ? c[0] : c[1]));
-  } else {
-    static_assert(N == 8, "16 or 8 requests");
+  } else if constexpr (N == 8) {
     d = vmin(b3 ? w[1] : w[0], dppf<kDppRor8>(b3 ? w[0] : w[1]));
+    d = vmin(d, dppf<kDppHalfMirror>(d));
+  } else {
+    static_assert(N == 4, "16, 8 or 4 requests");
+    d = vmin(w[0], dppf<kDppRor8>(w[0]));
     d = vmin(d, dppf<kDppHalfMirror>(d));
   }
   d = vmin(d, dppf<kDppQuad2301>(d));
@@ -615,7 +632,7 @@ __device__ __forceinline__ unsigned first_lane(unsigned long long m, int &count)
 struct Req {
   int r;                         // request index
   int off;                       // offset of its prefill row, -1: no prompt
-  float st, sb, rl, lout;        // SLOs, 1 / Lout (0: outside [1, 2^40]), Lout
+  float st, sb, rl, lout;        // SLOs, 1 / Lout (0: not decided on keys), Lout
 };
 
 __device__ __forceinline__ void put_result(const FrontArgs &a, int r, bool found, int index, float e) {
@@ -629,7 +646,7 @@ template <int N>
 __device__ __forceinline__ void choose_front(const FrontArgs &a, int2 info, bool sel, float sb, const Req &rq, v2f *Q) {
   constexpr int L = kWave / N;                   // lanes per request
   const int lane = threadIdx.x & (kWave - 1);
-  const int nA = info.x & 0xff, nB = (info.x >> 8) & 0xff, last = (info.x >> 16) - 1;
+  const int nA = info.x & 0xff, nB = (info.x >> 8) & 0xff, last = ((info.x >> 16) & 0xff) - 1;
   const gptr<v4f> f = scalar_ptr(a.front + (size_t)info.y * kWave);
   const gptr<v4f> fB = scalar_ptr(f + last * kWave);
   const int off = sel ? rq.off : 0;              // an unselected request reads the first row
@@ -729,105 +746,307 @@ __device__ __forceinline__ void choose_front(const FrontArgs &a, int2 info, bool
   if (sel && lane % L == 0) put_result(a, rq.r, best != INT_MAX, best, rq.lout * Kl);
 }
 
-// The selected requests against every GPU hosting the model, four requests at a time: for
-// requests that the fronts do not serve.  A request is decided on keys, as its bucket's front
-// would decide it, or (no prompt, Lout outside [1, 2^40], or a prompt row with tiny entries) on
-// energies E = fma(Lout, Y, Pp * TTFT): by its own fields only, so that its result does not
-// depend on whether its bucket has a front.  Lanes are cells (levels 0-3 and 4-7), each keeping
-// its least (key or E, GPU).
-__device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, unsigned long long sel, int L, const Req &rq,
+// ------------------------------------------------------------------ against every hosting GPU
+// A candidate's key (kByKey: x = TTFT / Lout) or energy (kByEnergy: x = TTFT; kNoPrompt: x = Pp * TTFT,
+// TTFT being the GPU's): both passes evaluate exactly these operations, and the one-launch kernel too.
+template <int KIND>
+__device__ __forceinline__ float all_value(float Pp, float Y, float x, float lout) {
+  if constexpr (KIND == kByKey) return fmaf(Pp, x, Y);
+  return fmaf(lout, Y, KIND == kNoPrompt ? x : Pp * x);
+}
+
+// Up to 64 hosts of one (wave, model), one per lane.
+struct Hosts {
+  int n, g, caps, row;           // row: offset of the host's batch row
+  float kap;                     // a host without candidates: NaN, so that no value on it compares
+};
+
+__device__ __forceinline__ Hosts load_hosts(const FrontArgs &a, int m, int w, int c0, int n) {
+  const int lane = threadIdx.x & (kWave - 1);
+  Hosts o;
+  o.n = min(kWave, n - c0);
+  const int2 h = a.hosts[(size_t)m * a.G + c0 + min(lane, o.n - 1)];
+  const int B = a.batch[(size_t)w * a.G + h.x];
+  const int bb = min(B, kRows - 1) + 1;
+  o.g = h.x;
+  o.caps = h.y & 63;
+  o.kap = B >= 0 ? a.kdyn[h.x] * ((float)bb * 0.03125f) : kMask;
+  o.row = max(bb - 1, 0) * kCells;
+  return o;
+}
+
+// The SLOs and Lout of a wavefront's N requests: st0, sb0 where the selected ones share theirs (one),
+// else lane 64 / N * q holds those of request q (read where they are used: as scalars, all of them
+// would leave k_choose short of registers).
+template <int N>
+struct AllSlos {
+  bool one;
+  float st0, sb0, st, sb, lout[N];
+};
+
+// This lane's cells under one pair of SM caps, remade where the caps change (hosts are grouped by them).
+struct Cells {
+  int caps = -1;
+  unsigned p[2], d[2];           // cells of the prefill and of the decode latency
+  float pdp[2], pdd[2];          // their power factors
+
+  __device__ __forceinline__ void set(int c, const float *s_pd) {
+    if (c == caps) return;
+    caps = c;
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int j = (lane >> 4) + 4 * r;
+      p[r] = min(j, c & 7) * 16 + (lane & 15);
+      d[r] = min(j, c >> 3) * 16 + (lane & 15);
+      pdp[r] = s_pd[p[r]];
+      pdd[r] = s_pd[d[r]];
+    }
+  }
+};
+
+// U hosts (from i0 on) at this lane's two cells: powers, and the table entries, all requested together.
+template <int U, int KIND>
+struct Entries {
+  int caps[U];
+  float Pp[U][2], Pd[U][2], tb[U][2], tt[U][2];
+
+  __device__ __forceinline__ void load(const Hosts &h, gptr<float> dcm, gptr<float> pfm, const float *s_pd, float p0,
+                                       Cells &c, int i0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + u, h.n - 1);
+      const int row = __builtin_amdgcn_readlane(h.row, i);
+      caps[u] = __builtin_amdgcn_readlane(h.caps, i);
+      // (a host past the last repeats it without power: no value on it compares)
+      const float kap = i0 + u < h.n ? lane_f(h.kap, i) : kMask;
+      c.set(caps[u], s_pd);
+      const gptr<float> d = scalar_ptr(dcm + row), p = scalar_ptr(pfm + row);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        tb[u][r] = d[c.d[r]];
+        if (KIND == kNoPrompt) tt[u][r] = p[c.p[r]];
+        Pp[u][r] = fmaf(kap, c.pdp[r], p0);
+        Pd[u][r] = fmaf(kap, c.pdd[r], p0);
+      }
+    }
+  }
+};
+
+// The least values over the chunk's hosts at this lane's two cells, into acc: the table entries of four
+// hosts are requested together (four wavefronts per SIMD hide the trip), two hosts scored at a time.
+// The prompt terms under a host's caps are fetched from their lanes where the caps change.
+template <int N, int KIND>
+__device__ __forceinline__ void all_hosts(const Hosts &h, gptr<float> dcm, gptr<float> pfm, const float *s_pd, float p0,
+                                          const AllSlos<N> &slo, const float (&xA)[N], const float (&xB)[N],
+                                          float (&acc)[N]) {
+  constexpr int U = 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  float x[2][N];
+  int now = -1;
+  Cells cells;
+  Entries<U, KIND> e;
+  // hosts [u, u + two] at cell r; those of a pair have the same caps if requests have prompts
+  const auto score = [&](int u, auto two, int r) {
+    constexpr int T = decltype(two)::value;
+    float Y[T], X[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const float tb = e.tb[u + t][r], tt = KIND == kNoPrompt ? e.tt[u + t][r] : 0.f;
+      X[t] = e.Pp[u + t][r] * tt;
+      Y[t] = e.Pd[u + t][r] * tb;
+      if (slo.one) {
+        Y[t] = tb < slo.sb0 && (KIND != kNoPrompt || tt < slo.st0) ? Y[t] : kMask;
+        asm volatile("" : "+v"(Y[t]));             // (else every value would be masked, not this one)
+      }
+    }
+    const auto value = [&](int t, int q, float y) {
+      return all_value<KIND>(e.Pp[u + t][r], y, KIND == kNoPrompt ? X[t] : x[r][q], slo.lout[q]);
+    };
+    const auto masked = [&](int t, int q) {
+      if (slo.one) return Y[t];
+      constexpr int L = kWave / N;
+      const bool in = e.tb[u + t][r] < lane_f(slo.sb, L * q) &&
+                      (KIND != kNoPrompt || e.tt[u + t][r] < lane_f(slo.st, L * q));
+      return in ? Y[t] : kMask;
+    };
+    if (slo.one) {
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        acc[q] = T == 2 ? vmin3(acc[q], value(0, q, Y[0]), value(T - 1, q, Y[T - 1])) : vmin(acc[q], value(0, q, Y[0]));
+    } else {
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        acc[q] = T == 2 ? vmin3(acc[q], value(0, q, masked(0, q)), value(T - 1, q, masked(T - 1, q)))
+                        : vmin(acc[q], value(0, q, masked(0, q)));
+    }
+  };
+  const auto upper = [](int caps) { return max(caps & 7, caps >> 3) >= 4; };   // else cell 1 repeats a lower level's
+  const auto terms = [&](int caps) {
+    if (KIND == kNoPrompt || caps == now) return;
+    now = caps;
+    const int cp = caps & 7;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const int from = ((min((lane >> 4) + 4 * r, cp) & 3) * 16 + (lane & 15)) << 2;
+#pragma unroll
+      for (int q = 0; q < N; ++q)
+        x[r][q] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(r == 0 || cp < 4 ? xA[q] : xB[q])));
+    }
+  };
+  for (int i0 = 0; i0 < h.n; i0 += U) {
+    e.load(h, dcm, pfm, s_pd, p0, cells, i0);
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      if (KIND == kNoPrompt || e.caps[u] == e.caps[u + 1]) {
+        terms(e.caps[u]);
+        score(u, std::integral_constant<int, 2>{}, 0);
+        if (upper(e.caps[u]) || upper(e.caps[u + 1])) score(u, std::integral_constant<int, 2>{}, 1);
+      } else {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          terms(e.caps[u + t]);
+          score(u + t, std::integral_constant<int, 1>{}, 0);
+          if (upper(e.caps[u + t])) score(u + t, std::integral_constant<int, 1>{}, 1);
+        }
+      }
+    }
+  }
+}
+
+// The selected requests (of up to N; all of one bucket and kind) against every GPU hosting the model:
+// for requests that the fronts do not serve.  A request is decided on keys where its bucket's front
+// would decide it so, by its own fields only, so that its result does not depend on whether there is
+// a front.  Lanes are cells (levels 0-3, then 4-7); then lanes are hosts, and each request's tied cells
+// are evaluated on all of them for the lowest index.
+template <int N, int KIND>
+__device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, bool sel, const Req &rq, v2f *Q,
                                            const float *s_pd) {
+  constexpr int L = kWave / N;                     // lanes per request
   const int lane = threadIdx.x & (kWave - 1);
   const int w = bucket / a.M, m = bucket - w * a.M;
   const int n = ro(a.host_cnt)[m];
   const float p0 = a.p0;
-  const float *dcm = a.dc + (size_t)m * kRows * kCells;
-  const unsigned pfm = (unsigned)m * kRows * kCells;
-  const int k = lane & 15;
-  sel &= L == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;   // bit L * q: request q
-  while (sel) {
-    int ql[4];
-    float lo[4], rl[4], st[4], sb[4];              // rl: 1 / Lout of a request decided on keys, else 0
-    int off[4];
-    for (int q = 0; q < 4; ++q) {
-      ql[q] = sel ? __builtin_ctzll(sel) : -1;
-      const int l = max(ql[q], 0);
-      lo[q] = lane_f(rq.lout, l);
-      rl[q] = lane_f(rq.rl, l);
-      st[q] = ql[q] >= 0 ? lane_f(rq.st, l) : -kInf;
-      sb[q] = lane_f(rq.sb, l);
-      off[q] = __builtin_amdgcn_readlane(rq.off, l);
-      if (off[q] >= 0) {
-        const float v0 = fabsf(a.pf[(unsigned)(off[q] + lane)]), v1 = fabsf(a.pf[(unsigned)(off[q] + kWave + lane)]);
-        if (__ballot((v0 > 0.f && v0 < kTinyLatency) || (v1 > 0.f && v1 < kTinyLatency)) != 0ull) rl[q] = 0.f;
-      } else {
-        rl[q] = 0.f;
-      }
-      sel &= sel - 1;
-    }
-    float be[2][4];
-    int bg[2][4];
+  const gptr<float> dcm = scalar_ptr(a.dc + (size_t)m * kRows * kCells), pfm = scalar_ptr(a.pf + (size_t)m * kRows * kCells);
+  const float st = sel ? rq.st : -kInf;            // an unselected request is masked
+  AllSlos<N> slo;
+  {
+    const int l0 = __builtin_ctzll(__ballot(sel));
+    slo.st = st;
+    slo.sb = rq.sb;
+    slo.st0 = lane_f(st, l0);
+    slo.sb0 = lane_f(rq.sb, l0);
+    const bool other = __float_as_int(rq.sb) != __float_as_int(slo.sb0) ||
+                       (KIND == kNoPrompt && __float_as_int(st) != __float_as_int(slo.st0));
+    slo.one = __ballot(sel && other) == 0ull;
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int q = 0; q < N; ++q) slo.lout[q] = lane_f(rq.lout, L * q);
+  }
+  float xA[N], xB[N], acc[N];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        be[u][q] = kInf;
-        bg[u][q] = INT_MAX;
-      }
-    for (int c0 = 0; c0 < n; c0 += kWave) {
-      const int nc = min(kWave, n - c0);
-      const int2 h = a.hosts[(size_t)m * a.G + c0 + min(lane, nc - 1)];
-      const int B = a.batch[(size_t)w * a.G + h.x];
-      const int bb = min(B, kRows - 1) + 1;
-      // a GPU without candidates: NaN power, so no energy on it compares below another
-      const float kapv = B >= 0 ? a.kdyn[h.x] * ((float)bb * 0.03125f) : kMask;
-      const int rowv = max(bb - 1, 0) * kCells;
-#pragma unroll 2
-      for (int i = 0; i < nc; ++i) {
-        const int row = __builtin_amdgcn_readlane(rowv, i);
-        const int caps = __builtin_amdgcn_readlane(h.y, i), g = __builtin_amdgcn_readlane(h.x, i);
-        const float kap = lane_f(kapv, i);
-        const int cp = caps & 7, cd = (caps >> 3) & 7;
+  for (int q = 0; q < N; ++q) acc[q] = kInf;
+  if constexpr (KIND != kNoPrompt) {
+    if (lane % L == 0) Q[lane / L] = v2f{st, rq.rl};
+    wave_sync();
+    const int off = sel ? rq.off : 0;
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const int j = u * 4 + (lane >> 4);
-          const int cP = min(j, cp) * 16 + k, cD = min(j, cd) * 16 + k;
-          const float tbt = dcm[row + cD];
-          const float Pp = fmaf(kap, s_pd[cP], p0);
-          const float Y = fmaf(kap, s_pd[cD], p0) * tbt;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const float ttft = a.pf[(off[q] >= 0 ? (unsigned)off[q] : pfm + row) + cP];
-            const float E = rl[q] > 0.f ? fmaf(Pp, ttft * rl[q], Y) : fmaf(lo[q], Y, Pp * ttft);
-            const bool ok = ttft < st[q] && tbt < sb[q] && (E < be[u][q] || (E == be[u][q] && E < kInf && g < bg[u][q]));
-            be[u][q] = ok ? E : be[u][q];
-            bg[u][q] = ok ? g : bg[u][q];
-          }
-        }
-      }
+    for (int q = 0; q < N; ++q) {
+      const gptr<float> p = scalar_ptr(a.pf + (unsigned)__builtin_amdgcn_readlane(off, L * q));
+      xA[q] = p[(unsigned)lane];
+      xB[q] = p[64u + (unsigned)lane];
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float e = be[0][q];
-      int id = bg[0][q] == INT_MAX ? INT_MAX : bg[0][q] * kCells + lane;
-      const int id1 = bg[1][q] == INT_MAX ? INT_MAX : bg[1][q] * kCells + 64 + lane;
-      if (be[1][q] < e || (be[1][q] == e && id1 < id)) {
-        e = be[1][q];
-        id = id1;
-      }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) {
-        const float oe = __shfl_xor(e, o, kWave);
-        const int oi = __shfl_xor(id, o, kWave);
-        if (oe < e || (oe == e && oi < id)) {
-          e = oe;
-          id = oi;
-        }
-      }
-      const float energy = rl[q] > 0.f ? lo[q] * e : e;
-      if (ql[q] >= 0 && lane == ql[q]) put_result(a, rq.r, id != INT_MAX && energy < kInf, id, energy);
+    for (int q = 0; q < N; ++q) {
+      const float sq = Q[q].x, rl = KIND == kByKey ? Q[q].y : 1.f;
+      xA[q] = xA[q] < sq ? xA[q] * rl : kMask;
+      xB[q] = xB[q] < sq ? xB[q] * rl : kMask;
+      if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if (n == 0) {
+    if (sel && lane % L == 0) put_result(a, rq.r, false, -1, kInf);
+    return;
+  }
+  const int last = (n - 1) & ~(kWave - 1);         // the last chunk of 64 hosts
+  Hosts h;
+  for (int c0 = 0; c0 <= last; c0 += kWave) {
+    h = load_hosts(a, m, w, c0, n);
+    all_hosts<N, KIND>(h, dcm, pfm, s_pd, p0, slo, xA, xB, acc);
+  }
+  const float Kl = wave_min<N>(acc);               // request lane / L
+  const float energy = KIND == kByKey ? rq.lout * Kl : Kl;
+  const float Ks = sel && Kl < kInf && energy < kInf ? Kl : kMask;   // NaN: infeasible
+#pragma unroll
+  for (int q = 0; q < N; ++q) {                    // the lanes that attain a request's least value
+    const unsigned long long tied = __ballot(acc[q] == lane_f(Ks, L * q));
+    if (lane == 0) Q[q] = v2f{__uint_as_float((unsigned)tied), __uint_as_float((unsigned)(tied >> 32))};
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  wave_sync();
+  int best = INT_MAX;
+  for (int c0 = last; c0 >= 0; c0 -= kWave) {      // (the last chunk's hosts are at hand)
+    if (c0 != last) h = load_hosts(a, m, w, c0, n);
+    const int cp = h.caps & 7, cd = h.caps >> 3;
+    constexpr int U = 4;                           // requests whose table entries are requested together
+#pragma unroll
+    for (int q0 = 0; q0 < N; q0 += U) {
+      unsigned long long tied[U];
+      unsigned long long any = 0ull;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const v2f t = Q[q0 + u];
+        tied[u] = ((unsigned long long)(unsigned)uniform(__float_as_int(t.y)) << 32) | (unsigned)uniform(__float_as_int(t.x));
+        any |= tied[u];
+      }
+      while (any) {                                // once, unless a request attains its value in several lanes
+        float tb[U][2], tt[U][2];
+        any = 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int c = tied[u] ? __builtin_ctzll(tied[u]) : 0;
+          const int off = __builtin_amdgcn_readlane(rq.off, L * (q0 + u));
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const int cP = min((c >> 4) + 4 * r, cp) * 16 + (c & 15), cD = min((c >> 4) + 4 * r, cd) * 16 + (c & 15);
+            tb[u][r] = dcm[(unsigned)(h.row + cD)];
+            tt[u][r] = KIND == kNoPrompt ? pfm[(unsigned)(h.row + cP)] : a.pf[(unsigned)(max(off, 0) + cP)];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int q = q0 + u, c = tied[u] ? __builtin_ctzll(tied[u]) : 0;
+          const float K = tied[u] ? lane_f(Ks, L * q) : kMask, lout = lane_f(rq.lout, L * q);
+          const float sq = lane_f(rq.st, L * q), sb = lane_f(rq.sb, L * q), rl = KIND == kByKey ? lane_f(rq.rl, L * q) : 1.f;
+          int id = INT_MAX;
+#pragma unroll
+          for (int r = 0; r < 2; ++r) {
+            const int cell = c + kWave * r;
+            const int cP = min(cell >> 4, cp) * 16 + (c & 15), cD = min(cell >> 4, cd) * 16 + (c & 15);
+            const float Pp = fmaf(h.kap, s_pd[cP], p0), Y = fmaf(h.kap, s_pd[cD], p0) * tb[u][r];
+            const float x = KIND == kNoPrompt ? Pp * tt[u][r] : (KIND == kByKey ? tt[u][r] * rl : tt[u][r]);
+            const bool hit = lane < h.n && tt[u][r] < sq && tb[u][r] < sb && all_value<KIND>(Pp, Y, x, lout) == K;
+            for (unsigned long long b = __ballot(hit); b; b &= b - 1)
+              id = min(id, __builtin_amdgcn_readlane(h.g, __builtin_ctzll(b)) * kCells + cell);
+          }
+          best = lane / L == q ? min(best, id) : best;
+          tied[u] &= tied[u] - 1;
+          any |= tied[u];
+        }
+      }
+    }
+  }
+  if (sel && lane % L == 0) put_result(a, rq.r, best != INT_MAX, best, energy);
+}
+
+template <int N>
+__device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, int kind, bool sel, const Req &rq, v2f *Q,
+                                           const float *s_pd) {
+  if (kind == kNoPrompt)
+    choose_all<N, kNoPrompt>(a, bucket, sel, rq, Q, s_pd);
+  else if (kind == kByEnergy)
+    choose_all<N, kByEnergy>(a, bucket, sel, rq, Q, s_pd);
+  else
+    choose_all<N, kByKey>(a, bucket, sel, rq, Q, s_pd);
 }
 
 // The kernel's arguments (its only parameter) read again from the kernel-argument segment where
@@ -845,7 +1064,7 @@ __device__ __forceinline__ FrontArgs fresh_args() {
 __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
   __shared__ v4i s_rec[kChooseThreads];          // {row offset, TTFT SLO, TBT SLO, 1 / Lout}
   __shared__ float s_lout[kChooseThreads];
-  __shared__ int s_bkt[kChooseThreads];          // bucket * 2 + (no prompt, or Lout outside [1, 2^40])
+  __shared__ int s_bkt[kChooseThreads];          // bucket * 4 + kind
   __shared__ int2 s_info[kChooseThreads];        // its bucket's front
   __shared__ uint16_t s_ord[kChooseThreads];     // request of each sorted position
   __shared__ int s_cnt[kSlots];                  // requests per slot, then the slot's start
@@ -853,7 +1072,7 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
   __shared__ v2f s_q[kChooseThreads / kWave][kR];
   __shared__ float s_pd[kCells];
   __shared__ int s_sum[kChooseThreads / kWave];
-  __shared__ int s_next;
+  __shared__ int s_next, s_again, s_rest;
   const int per = (a.n_chunks + kXcds - 1) / kXcds;
   const int ck = (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
   if ((int)blockIdx.x / kXcds >= per || ck >= a.n_chunks) return;
@@ -862,7 +1081,7 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
   const int nreq = min(a.chunk, a.R - first);
   s_cnt[t] = 0;
   if (t < kCells) s_pd[t] = a.sm_level[t >> 4] * cube(a.freq_level[t & 15]);
-  if (t == 0) s_next = 0;
+  if (t == 0) s_next = s_again = s_rest = 0;
   int slot = -1, pos = 0;
   int2 info = make_int2(-1, 0);
   int m = -1, w = 0, pt = 0, pr = 0;
@@ -882,15 +1101,16 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
       const int bucket = w * a.M + m;
       const int row = pt > 0 ? m * kRows + prompt_row(pt) : 0;
       const float lout = (float)(((long long)pr * 105 + 99) / 100);
-      const float rl = lout >= 1.f && lout <= 0x1p40f ? 1.f / lout : 0.f;
-      const bool all = pt == 0 || rl == 0.f;
-      if (!all) info = a.info[bucket];
+      const float rl = pt > 0 && lout >= 1.f && lout <= 0x1p40f ? 1.f / lout : 0.f;
+      const int kind = pt == 0 ? kNoPrompt : (rl == 0.f ? kByEnergy : kByFront);
+      if (kind == kByFront) info = a.info[bucket];
       s_rec[t] = v4i{pt > 0 ? row * kCells : -1, __float_as_int(st), __float_as_int(sb), __float_as_int(rl)};
       s_lout[t] = lout;
-      s_bkt[t] = bucket * 2 + (all ? 1 : 0);
-      // requests of one bucket and TBT SLO share a slot; others may too
-      const unsigned h = (unsigned)__float_as_int(sb) * 0x9E3779B1u >> 29;
-      slot = (((unsigned)bucket * 8u + h) & (kSlots / 2 - 1)) << 1 | (all ? 1 : 0);
+      s_bkt[t] = bucket * 4 + kind;
+      // requests of one bucket and TBT SLO share a slot, those without a front of one bucket and kind;
+      // others may too
+      const unsigned h = kind == kByFront ? (unsigned)__float_as_int(sb) * 0x9E3779B1u >> 29 : (unsigned)kind;
+      slot = (((unsigned)bucket * 8u + h) & (kSlots / 2 - 1)) << 1 | (kind != kByFront ? 1 : 0);
       pos = atomicAdd(&s_cnt[slot], 1);
     } else {
       put_result(a, first + t, false, -1, kInf);
@@ -911,12 +1131,24 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
     tiles += s >> 16;
   }
   s_cnt[t] = ex & 0xffff;
+  if (slot >= 0 && (info.x & kOddRows)) {         // (info is used first here: nothing waits for it before)
+    if (s_rec[t].w != 0) {                         // decided on keys, unless its prompt row is an odd one
+      const float top = a.row_max[m * kRows + prompt_row(pt)];
+      if (top < 0.f) info.x = -1;
+      if (top == kRowTiny) s_rec[t].w = 0;
+      if (top < 0.f) s_bkt[t] += top == kRowTiny ? kByEnergy : kByKey;
+    }
+    if (info.x < 0) s_rest = 1;
+  }
   s_info[t] = info;
   for (int i = 0; i * kR < n; ++i)
     s_tile[(ex >> 16) + i] = (unsigned)((ex & 0xffff) + i * kR) | ((unsigned)min(kR, n - i * kR) << 16);
   __syncthreads();
   if (slot >= 0) s_ord[s_cnt[slot] + pos] = (uint16_t)t;
   __syncthreads();
+  const bool rest = uniform(s_rest) != 0;
+  // Requests with a front first; the others in a second round over the tiles, so that their path (which
+  // most calls never take) shares no registers with this one.
   for (;;) {
     int ti = 0;
     if (lane == 0) ti = atomicAdd(&s_next, 1);
@@ -924,28 +1156,53 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
     if (ti >= tiles) break;
     const unsigned tile = (unsigned)uniform((int)s_tile[ti]);
     const int nt = (int)(tile >> 16);
-    const int L = nt > 8 ? 4 : 8;                  // lanes per request: tiles of up to 16 or 8
-    const int q = nt > 8 ? lane >> 2 : lane >> 3;
+    const int q = nt > 8 ? lane >> 2 : lane >> 3;  // 4 or 8 lanes per request: tiles of up to 16 or 8
     const bool has = q < nt;
     const int i = s_ord[(tile & 0xffffu) + (has ? q : 0)];
     const v4i rec = s_rec[i];
     const Req rq{first + i, rec.x, __int_as_float(rec.y), __int_as_float(rec.z), __int_as_float(rec.w), s_lout[i]};
     const int bkt = s_bkt[i];
     const int2 in = s_info[i];
-    unsigned long long todo = __ballot(has);
+    unsigned long long todo = __ballot(has && in.x >= 0);
     while (todo) {
       const int ld = __builtin_ctzll(todo);
       const int b = __builtin_amdgcn_readlane(bkt, ld), sbi = __builtin_amdgcn_readlane(rec.z, ld);
       const bool sel = has && bkt == b && rec.z == sbi;      // as bits: a NaN SLO matches itself
-      const unsigned long long sm = __ballot(sel);
-      todo &= ~sm;
+      todo &= ~__ballot(sel);
       const int2 fr = make_int2(__builtin_amdgcn_readlane(in.x, ld), __builtin_amdgcn_readlane(in.y, ld));
-      if (fr.x < 0)
-        choose_all(fresh_args(), b >> 1, sm, L, rq, s_pd);
-      else if (nt > 8)
+      if (nt > 8)
         choose_front<16>(a, fr, sel, __int_as_float(sbi), rq, s_q[wv]);
       else
         choose_front<8>(a, fr, sel, __int_as_float(sbi), rq, s_q[wv]);
+    }
+  }
+  if (!rest) return;
+  for (;;) {
+    int ti = 0;
+    if (lane == 0) ti = atomicAdd(&s_again, 1);
+    ti = uniform(ti);
+    if (ti >= 2 * tiles) break;
+    // half a tile: with sixteen requests, as choose_front takes, the prompt terms under a host's caps
+    // would not fit the registers
+    const unsigned tile = (unsigned)uniform((int)s_tile[ti >> 1]);
+    const int nt = (int)(tile >> 16), q0 = (ti & 1) * 8;
+    if (q0 >= nt) continue;
+    const bool four = nt - q0 <= 4;
+    const int q = q0 + (four ? lane >> 4 : lane >> 3);
+    const bool has = q < nt;
+    const int i = s_ord[(tile & 0xffffu) + (has ? q : 0)];
+    const v4i rec = s_rec[i];
+    const Req rq{first + i, rec.x, __int_as_float(rec.y), __int_as_float(rec.z), __int_as_float(rec.w), s_lout[i]};
+    const int bkt = s_bkt[i];
+    unsigned long long todo = __ballot(has && s_info[i].x < 0);
+    while (todo) {
+      const int b = __builtin_amdgcn_readlane(bkt, __builtin_ctzll(todo));
+      const bool sel = has && bkt == b;
+      todo &= ~__ballot(sel);
+      if (four)
+        choose_all<4>(fresh_args(), b >> 2, b & 3, sel, rq, s_q[wv], s_pd);
+      else
+        choose_all<8>(fresh_args(), b >> 2, b & 3, sel, rq, s_q[wv], s_pd);
     }
   }
 }
@@ -986,7 +1243,7 @@ bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests 
   o->host_cnt = take(sizeof(int32_t) * M);
   o->hosts = take(sizeof(int2) * M * Gn);
   o->rowle = take(sizeof(uint32_t) * M * kRows);
-  o->model_flags = take(sizeof(int32_t) * M);
+  o->dc_positive = take(sizeof(int32_t) * M);
   o->row_max = take(sizeof(float) * M * kRows);
   o->info = take(sizeof(int2) * buckets);
   o->pool_used = take(sizeof(int32_t));
@@ -1035,7 +1292,7 @@ festina_status launch(const festina_lut *L, const festina_gpus *G, const festina
   a.host_cnt = reinterpret_cast<int32_t *>(ws + lay.host_cnt);
   a.hosts = reinterpret_cast<int2 *>(ws + lay.hosts);
   a.rowle = reinterpret_cast<uint32_t *>(ws + lay.rowle);
-  a.model_flags = reinterpret_cast<int32_t *>(ws + lay.model_flags);
+  a.dc_positive = reinterpret_cast<int32_t *>(ws + lay.dc_positive);
   a.row_max = reinterpret_cast<float *>(ws + lay.row_max);
   a.info = reinterpret_cast<int2 *>(ws + lay.info);
   a.pool_used = reinterpret_cast<int32_t *>(ws + lay.pool_used);

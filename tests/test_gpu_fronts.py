@@ -124,6 +124,28 @@ def test_requests_scored_against_every_gpu():
     parity(inp, "unusual requests and tables")
 
 
+@pytest.mark.parametrize("one_slo", [False, True])
+@pytest.mark.parametrize("R,kind", [(1, "no prompt"), (20, "no prompt"), (40, "no output"), (70, "no prompt"),
+                                    (130, "no prompt"), (130, "no output"), (130, "tiny row"), (130, "negative row")])
+def test_requests_without_a_front(R, kind, one_slo):
+    """Groups of up to 4, 8 and 16 requests that every hosting GPU is scored for (1,025 of 4,100: several
+    rounds of 64, the last one partly filled), with and without one SLO per group, capped GPUs."""
+    inp = W.make_placement(2, n_requests=R, n_gpus=4100)
+    rng, q, g = np.random.default_rng(R), inp["requests"], inp["gpus"]
+    g["cap_pf"], g["cap_dc"] = (rng.integers(0, 8, 4100).astype(np.int8) for _ in range(2))
+    q["model"] %= 3
+    if kind == "no prompt":
+        q["prompt_tokens"][:] = 0
+    elif kind == "no output":
+        q["pred_out_tokens"][:] = 0
+    else:
+        inp["lut"]["pf"][:, :, 3, 7] = 1e-30 if kind == "tiny row" else -0.5
+    if not one_slo:
+        q["slo_ttft_ms"] *= rng.uniform(0.3, 1.5, R).astype(np.float32)
+        q["slo_tbt_ms"] *= rng.uniform(0.3, 1.5, R).astype(np.float32)
+    parity(inp, f"{kind}, one SLO={one_slo}")
+
+
 def test_slo_values():
     """TBT SLOs different for every request of a group, and infinite, zero or NaN SLOs."""
     inp = tiny(42, R=3300, M=1, W=1, caps=True)

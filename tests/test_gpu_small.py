@@ -97,3 +97,23 @@ def test_same_results_where_requests_have_no_front(entry):
         big["gpus"]["batch"][:] = np.arange(200, dtype=np.int32) % 32
         q["slo_tbt_ms"][:] = 32.0
     same_in_a_small_call(big)
+
+
+@pytest.mark.parametrize("caps", [False, True])
+@pytest.mark.parametrize("p0", [0.0, 100.0])
+def test_same_results_with_negative_latencies(caps, p0):
+    """Negative decode entries turn the order of their rows' Y between hosts, and may make Y and keys
+    negative; negative and tiny prefill entries in some rows only.  One -inf entry, and GPUs of negative power.  Bit for bit the
+    one-launch kernel's results, which drops no candidate (energies near zero cancel, so they have
+    no bound relative to float64)."""
+    inp = W.make_placement(4 if caps else 3, seed=77, n_requests=20000, n_gpus=150)
+    lut, rng = inp["lut"], np.random.default_rng(43)
+    lut["p0_w"] = p0
+    lut["dc"][::2, 2:9:3] -= np.float32(60.0)
+    lut["dc"][1, 4, 3, 7] = -np.inf
+    lut["dc"][1::4][rng.random(lut["dc"][1::4].shape) < 0.01] = np.float32(-3.0)
+    lut["pf"][::3, ::5, 4, 9] = np.float32(-2.0)
+    lut["pf"][1::3, ::7, 2, 3] = np.float32(1e-30)
+    inp["gpus"]["k_dyn_w"][::9] = 0.0
+    inp["gpus"]["k_dyn_w"][5::11] = -40.0
+    same_in_a_small_call(inp, 5000)

@@ -2317,10 +2317,16 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // against the kernels below for 4 x 8 tables: 64 on 8 7.6 / 19.7, 16,384 on 8 (2^17) 14.8 / 25.4,
 // 16,384 on 32 (2^19) 33.0 / 39.3.  (All with 2.7 us more host time per call than now: calls below
 // 8 us were the host's.)
+// GPUs that hold more models than that, all 32 here: k_small, front search, kernels below.  Up to 2^18
+// (request, GPU) pairs k_small stays ahead or level: 256 on 1,024 29 / 154 / 85, 1,024 on 256 28 / 34 /
+// 38, 4,096 on 64 28 / 23 / 30; past them it is behind: 1,024 on 1,024 100 / 158 / 106, 4,096 on 128 52 /
+// 26 / 32, 4,096 on 256 100 / 34 / 41, 16,384 on 64 87 / 23 / 39.  The line stays where fleets of up to
+// 4 models per GPU have it (4,096 on 256: 18.2 / 21.1 / 28).
 // With too few requests per (wave, model) for the front search (`sparse`) the 8 x 16 kernel's tiles of
 // 16 requests stay mostly empty, and k_small serves larger calls too: 6,007 requests in 4,200
 // buckets on 600 GPUs 35 / 104, 20,000 in 8,192 on 512 GPUs 113 / 193, 100,000 in 32,768 on 512
-// GPUs (2^22.6 pairs) 456 / 546.
+// GPUs (2^22.6 pairs) 456 / 546; all 64 models on every GPU (16 times the pairs counted): 8,192 in 3,840
+// on 4,096 GPUs 2,744 / 7,180, 32,768 in 10,240 on 4,096 9,990 / 13,340.
 constexpr long long kSmallPairs = 1 << 17, kSparsePairs = 1 << 23;
 constexpr int kSmallMaxGpus = 4096;
 inline bool small_call(long long M, long long G, long long R, bool fast, bool sparse) {

@@ -328,7 +328,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   __shared__ float s_pd[kCells];                 // s_j * f_k^3
   __shared__ uint32_t s_rl[kRows];
   __shared__ float s_pmin[2];
-  __shared__ int s_bad[2], s_n[2], s_cnt[2];
+  __shared__ int s_bad[2], s_n[2], s_cnt[2], s_long;
   const int bucket = blockIdx.x;
   const int w = bucket / a.M, m = bucket - w * a.M;
   const int t = threadIdx.x, lane = t & (kWave - 1), r = uniform(t >> 6);
@@ -338,6 +338,7 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
   const float pd = a.sm_level[t >> 4] * cube(a.freq_level[t & 15]);
   if (t < kRows) s_rl[t] = a.rowle[m * kRows + t];
   s_pd[t] = pd;
+  if (t == 0) s_long = 0;
   {
     float mn = pd;
 #pragma unroll
@@ -405,7 +406,12 @@ __global__ void __launch_bounds__(kFrontBlock) k_fronts(FrontArgs a) {
     bad = bad || kap < -kMaxFactor;
     const uint32_t rl = kap >= 0.f ? s_rl[row] : 0u;   // (negative powers turn the order of Y, too)
     s_h[t] = v4i{__float_as_int(kap), g, row, (int)rl};
+    if (c0 > 0 && cnt > 255) s_long = 1;
     __syncthreads();
+    if (c0 > 0 && s_long) {                        // too long to keep: scored against every host
+      bad = true;
+      break;
+    }
     // dropped where one host of its class is no worse on every cell
     bool keep = kap == kap;
     if (t < nc && rl != 0u) {
@@ -1225,12 +1231,15 @@ bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests 
   if (L->n_sm != kNS || L->n_freq != kNF || M > INT_MAX / (2 * kRows * kCells) || Gn > (1 << 24)) return false;
   const long long buckets = W * M;
   if (sparse(buckets, R)) return false;
-  // steps per bucket: 16 at most (fronts of the capped, 1,024-GPU fleets take 4.6 on average and 8 at
-  // the 99th percentile), less where the buckets do not leave room beside the host lists
+  // steps per bucket: 16 (fronts of the capped, 1,024-GPU fleets take 4.6 on average and 8 at the
+  // 99th percentile), up to 255 for few buckets (with many hosts some fronts are longer, and were built
+  // twice: 32 models of 1,024 hosts each 112 -> 68 us, of 3,900 588 -> 344), less where the buckets
+  // do not leave room beside the host lists
   const long long step = kWave * (long long)sizeof(v4f);
   const long long room = (31LL << 20) - (long long)sizeof(int2) * M * Gn - 16 * buckets - 512 * M;
   const long long fit = room / (buckets * step);
-  const int cap = (int)(fit <= 16 ? fit - 1 : 16);   // the rest is the pool of longer fronts
+  const long long want = buckets > 1024 ? 16 : (buckets <= 64 ? 255 : 16384 / buckets);
+  const int cap = (int)(fit <= want ? fit - 1 : want);   // the rest is the pool of longer fronts
   if (room <= 0 || cap < 8) return false;
   const long long left = room / step - cap * buckets;
   const long long pool = left < 4096 ? left : 4096;
@@ -1253,8 +1262,9 @@ bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests 
   o->buckets = (int32_t)buckets;
   o->cap = cap;
   o->pool_steps = (int32_t)pool;
-  const long long c = ((R + 255) / 256 + 63) & ~63LL;
-  o->chunk = (int32_t)(c < 128 ? 128 : (c > kChooseThreads ? kChooseThreads : c));
+  // (with many hosts per model, requests without a front take long: few requests go to more workgroups)
+  const long long c = ((R + 255) / 256 + 63) & ~63LL, least = (M <= 4 ? Gn : 4 * Gn / M) > 384 ? 16 : 128;
+  o->chunk = (int32_t)(R <= 256 * least ? least : (c > kChooseThreads ? kChooseThreads : (c < 64 ? 64 : c)));
   return true;
 }
 

@@ -91,7 +91,7 @@ def test_same_results_where_requests_have_no_front(entry):
     elif entry == "no prompt, no output":
         q["prompt_tokens"][::3] = 0
         q["pred_out_tokens"][::4] = 0
-    else:                                           # 2,048 fronts of some 16 steps, one host each per row
+    else:                                           # 2,048 fronts of 32 steps or more
         big["gpus"]["resident"][:] = 0xffffffff
         lut["dc"][:] = 30.0 - 0.5 * np.arange(32, dtype=np.float32)[None, :, None, None]
         big["gpus"]["batch"][:] = np.arange(200, dtype=np.int32) % 32

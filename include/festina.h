@@ -165,7 +165,9 @@ festina_status festina_score_placements(const festina_lut *lut, const festina_gp
 /* For callers that time the scoring kernel alone (a measurement, not part of the search):
  * festina_score_placements, with `score_begin` recorded on `stream` immediately before
  * the scoring kernel and `score_end` immediately after it, so that hipEventElapsedTime of
- * the two is that kernel's duration.  Each is a hipEvent_t passed as void*, created by the
+ * the two is that kernel's duration.  (Where a front search serves the call, they are
+ * recorded around its three kernels, which score and rule out candidates between them.)
+ * Each is a hipEvent_t passed as void*, created by the
  * caller on the current device; NULL leaves that point unrecorded (both NULL: exactly
  * festina_score_placements).  Same arguments, checks, outputs and errors otherwise; a
  * failing record returns FESTINA_ERR_DEVICE.  Each recorded event costs a few microseconds

@@ -23,7 +23,7 @@ bool sparse(long long buckets, long long R);
 bool layout(const festina_lut *L, const festina_gpus *G, const festina_requests *Q, Layout *o);
 
 // The launches of one call on a checked workspace of lay.total bytes; ev_begin / ev_end (or
-// nullptr) are recorded around the choosing kernel.
+// nullptr) are recorded around all three: each of them rules candidates out.
 festina_status launch(const festina_lut *L, const festina_gpus *G, const festina_requests *Q,
                       const festina_placements *out, const Layout &lay, char *ws, void *stream, void *ev_begin,
                       void *ev_end);

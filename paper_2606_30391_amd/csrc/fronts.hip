@@ -1309,11 +1309,11 @@ festina_status launch(const festina_lut *L, const festina_gpus *G, const festina
   a.pool_steps = lay.pool_steps;
   a.front = reinterpret_cast<v4f *>(ws + lay.front);
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (mark(ev_begin, st) != hipSuccess) return FESTINA_ERR_DEVICE;
   k_models<<<(1 + kRowParts + kRows / 4) * a.M, kModelBlock, 0, st>>>(a);
   if (hipGetLastError() != hipSuccess) return FESTINA_ERR_DEVICE;
   k_fronts<<<lay.buckets, kFrontBlock, 0, st>>>(a);
   if (hipGetLastError() != hipSuccess) return FESTINA_ERR_DEVICE;
-  if (mark(ev_begin, st) != hipSuccess) return FESTINA_ERR_DEVICE;
   const int grid = (a.n_chunks + kXcds - 1) / kXcds * kXcds;
   k_choose<<<grid, kChooseThreads, 0, st>>>(a);
   if (hipGetLastError() != hipSuccess || mark(ev_end, st) != hipSuccess) return FESTINA_ERR_DEVICE;

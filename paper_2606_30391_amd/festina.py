@@ -290,7 +290,7 @@ class DevicePlacement:
 
     def run(self, stream=None, events=None):
         """One search; `events` = (begin, end) raw hipEvent_t handles recorded around the
-        scoring kernel (the timed entry point), else None."""
+        scoring kernel or kernels (the timed entry point), else None."""
         festina_score_placements(self.lut, self.gpus, self.req, self.out, self.workspace, self.ws_bytes, stream,
                                  events)
 

@@ -51,3 +51,24 @@ def test_timed_calls_around_the_scoring_kernels():
     _check(hip, dp.run, dp.results, "placement config 3")
     dm = F.DeviceMigration(W.make_fleet(), "cuda")
     _check(hip, dm.run, dm.results, "consolidation config 5")
+
+
+def test_timed_call_of_a_front_search_covers_its_kernels():
+    """256 requests on 16,384 GPUs: building the fronts takes nearly all of the call."""
+    import bench
+    from paper_2606_30391_amd import festina as F
+    hip = bench.Hip()
+    dp = F.DevicePlacement(W.make_placement(3, n_requests=256, n_gpus=16384), "cuda")
+    ev, whole = [hip.event(), hip.event()], [hip.event(), hip.event()]
+    st = torch.cuda.current_stream().cuda_stream
+    share = []
+    for _ in range(8):
+        hip.record(whole[0], st)
+        dp.run(events=tuple(ev))
+        hip.record(whole[1], st)
+        torch.cuda.synchronize()
+        share.append(hip.elapsed_ms(*ev) / hip.elapsed_ms(*whole))
+    for e in ev + whole:
+        hip.destroy(e)
+    print(f"[gpu] timed call: share of the call between the events {max(share):.2f}", flush=True)
+    assert max(share) > 0.6

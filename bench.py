@@ -50,7 +50,8 @@ SCLK_HZ = 2.4e9
 VALU_PEAK = N_CU * LANES_PER_CU_CLOCK * SCLK_HZ            # 39.32e12 lane-ops/s
 HBM_PEAK = 8.0e12                                           # B/s
 
-# Least VALU work per candidate of an exhaustive search: divided by the request's Lout, a
+# Least VALU work per candidate of a search that scores every one (k_small and the kernels of the
+# placement pipeline): divided by the request's Lout, a
 # candidate's energy is Pp * (TTFT / Lout) + Pd * TBT, one fused multiply-add of a request
 # term and two GPU terms, and a three-way min folds two candidates into the running minimum,
 # half an instruction each.  The count runs over distinct candidates: the cells of a capped
@@ -65,8 +66,8 @@ OPS_PER_CELL = 4.5
 # u_s + u_d, two multiplies, subtract, FMA, compare with the best, three selects.
 OPS_PER_PAIR = 15
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_score_config4_traffic.json")
-COUNTERS_FILE = os.path.join(ROOT, "profiles", "k_score_config4_counters.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "front_search_config4_traffic.json")
+COUNTERS_FILE = os.path.join(ROOT, "profiles", "front_search_config4_counters.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_2606_30391_amd", "csrc", "festina.hip")
 FRONTS_SRC = os.path.join(ROOT, "paper_2606_30391_amd", "csrc", "fronts.hip")
 SWEEP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_sweep_traffic.json")
@@ -134,10 +135,22 @@ def placement_candidates(inp, sel=None):
     return int(hosts[model[ok]].sum()) * lut["n_sm"] * lut["n_freq"]
 
 
+def placement_route(inp):
+    """The search that serves a call of these shapes with its full workspace, by the library's rules
+    (small_call in festina.hip, festina_fronts::layout but for its workspace limits)."""
+    lut, G, R = inp["lut"], inp["gpus"]["n_gpus"], inp["requests"]["n_requests"]
+    M, buckets = lut["n_models"], inp["gpus"]["n_waves"] * lut["n_models"]
+    fast = lut["n_sm"] == 8 and lut["n_freq"] == 16
+    sparse = fast and buckets > 1024 + R // 4
+    hosts = G if M <= 4 else -(-4 * G // M)
+    if G <= 4096 and R * hosts <= (1 << 23 if sparse else 1 << 17 if fast else 1 << 18):
+        return "k_small"
+    return "front search" if fast and not sparse else "all candidates"
+
+
 def placement_ops(inp):
-    """Least VALU lane-operations of the search that serves these tables."""
-    lut = inp["lut"]
-    if lut["n_sm"] == 8 and lut["n_freq"] == 16:
+    """Least VALU lane-operations of the search that serves the call."""
+    if placement_route(inp) == "front search":
         return inp["requests"]["n_requests"] * 128 * OPS_PER_CELL
     return distinct_candidates(inp) * OPS_PER_CANDIDATE
 
@@ -196,8 +209,8 @@ def src_hash(path=KERNEL_SRC):
 
 
 def load_traffic(path=TRAFFIC_FILE, src=FRONTS_SRC):
-    """HBM bytes per launch of a kernel from the committed counter runs, or None when
-    the kernel source changed since they were taken."""
+    """HBM bytes per launch of a kernel (per call of the front search: its three) from the committed
+    counter runs, or None when the kernel source changed since they were taken."""
     try:
         d = json.load(open(path))
     except (OSError, ValueError):
@@ -208,15 +221,15 @@ def load_traffic(path=TRAFFIC_FILE, src=FRONTS_SRC):
 
 
 def load_counters(path=COUNTERS_FILE, src=FRONTS_SRC):
-    """VALU issue figures of the scoring kernel from the committed counter run, or None when
-    the kernel source changed since it was taken."""
+    """VALU issue figures of the front search's choosing kernel from the committed counter run, or
+    None when the kernel source changed since it was taken."""
     try:
         d = json.load(open(path))
     except (OSError, ValueError):
         return None
     if d.get("kernel_src_sha256_16") != src_hash(src):
         return None
-    return {"valu_issue_busy": d["valu_issue_busy"],
+    return {"kernel": d["kernel"], "valu_issue_busy": d["valu_issue_busy"],
             "valu_lane_ops_per_distinct_candidate": d["valu_lane_ops_per_distinct_candidate"],
             "sclk_ghz_effective": d["sclk_ghz_effective"]}
 
@@ -624,7 +637,7 @@ def main():
     torch.cuda.synchronize()
 
     # Timed steps: placement on the current stream, consolidation on the side stream; events
-    # are recorded around the scoring kernel only, in every SAMPLE-th step (each record costs
+    # are recorded around the placement kernels, in every SAMPLE-th step (each record costs
     # a few microseconds of stream time); the consolidation call is timed afterwards on its
     # own, as a batch.
     K = args.steps
@@ -662,8 +675,11 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
+        # candidates that a step decides on: the front search rules most of them out for a whole
+        # (wave, model) at once and evaluates some 1.1 per (request, cell)
+        "value_counts": "candidates covered",
         # the same step counted over distinct candidates only (a capped GPU's SM levels above
-        # max(cap_pf, cap_dc) repeat lower cells and are not evaluated)
+        # max(cap_pf, cap_dc) repeat lower cells)
         "value_distinct": (n_distinct + n_pairs) / step_s,
         "dtype": "f32",
         "data": "synthetic",
@@ -677,7 +693,8 @@ def main():
             "parallelism": "single GPU",
         },
         "roofline": {
-            "kernel": "k_choose (placement scoring against the candidate fronts + fused argmin)",
+            "kernel": "k_models + k_fronts + k_choose (front search: undominated candidates of each cell, "
+                      "then placement scoring against them + fused argmin)",
             "bound": "alu",
             "achieved": achieved / 1e12,
             "peak": VALU_PEAK / 1e12,
@@ -703,6 +720,7 @@ def main():
                          "ops_per_pair": OPS_PER_PAIR,
                          "traffic": load_traffic(MIGRATE_TRAFFIC_FILE, KERNEL_SRC)},   # both launches
         },
+        # k_score: the front search's three kernels (k_models, k_fronts, k_choose)
         "kernels_ms": {"k_score": score_ms, "k_score_candidates_per_s": n_cand / (score_ms * 1e-3),
                        "migration_call": mig_ms,
                        "migration_pairs_per_s_call": n_pairs / (mig_ms * 1e-3)},
@@ -806,7 +824,7 @@ def per_config(F, W, hip, torch, verbose=False):
         for e in ev:
             hip.destroy(e)
         cm, km = float(np.median(call_ms)), float(np.median(kern_ms))
-        timed = "scoring kernel (HIP events around it inside the library)"
+        timed = f"{placement_route(inp)} (HIP events around its kernels inside the library)" if cfg < 5 else ""
         if cfg == 5:
             # an event between the two migration kernels costs several microseconds of stream
             # time, more than the kernel itself: time a batch of whole calls instead

@@ -983,9 +983,9 @@ extern "C" size_t festina_dispatch_waves_workspace_bytes(const festina_lut *L, c
 
 // k_dispatch4 over requests lo .. hi-1.  A wave's kernel is a chain of memory round trips (the
 // previous wave's state comes from beyond the L2s): 64 lanes x 2 hosts take 128 hosts in one
-// chain.  Waves of 256 / 4,096 / 32,768 requests on 1,024 GPUs (80 hosts each): 7.8 / 14.9 / 65 us
-// per wave, against 10.4 / 14.7 / 71 with 32 lanes x 4, 17.5 / 18.8 / 76 with 16 x 4 and 12.2 /
-// 25.4 / 129 with k_dispatch's loop over single hosts.  On a small fleet most of 64 lanes would
+// chain.  Waves of 256 / 4,096 / 32,768 requests on 1,024 GPUs (80 hosts each) take 7.1 / 11.7 / 67 us
+// each; when the split was chosen 7.8 / 14.9 / 65, against 10.4 / 14.7 / 71 with 32 lanes x 4, 17.5 /
+// 18.8 / 76 with 16 x 4 and 12.2 / 25.4 / 129 with k_dispatch's loop over single hosts.  On a small fleet most of 64 lanes would
 // have no host: 4,096 requests on 128 GPUs take 10.9 us with 64 lanes, 9.9 with 16.  A launch holds
 // fewer than 2^32 threads, so waves of 2^26 requests or more take 16 lanes whatever the fleet.
 constexpr int kSmallFleet = 256, kNarrowRequests = 2048, kWidestRequests = (1 << 26) - 1;

@@ -1,9 +1,10 @@
 // festina.hip -- MI355X (gfx950) kernels and C-ABI host dispatch of the batched
 // energy-aware placement and migration search (Festina, Sec. 3.3 and Sec. 3.5).
 //
-// Placement searches of 8 x 16 tables with enough requests per (wave, model) go to the front
-// search in fronts.hip (the rule is festina_fronts::layout); all others run here:
-// Placement pipeline (one call, four launches on the caller's stream, five with k_scan):
+// Placement calls of few (request, GPU) pairs take one launch, k_small (the rule is small_call);
+// larger ones of 8 x 16 tables with enough requests per (wave, model) and workspace for it the front
+// search in fronts.hip (festina_fronts::layout); all others the placement pipeline (four launches
+// on the caller's stream, five with k_scan):
 //   k_init      clear the bucket counters; the table minima (least entry of each prefill
 //                 row, its least nonzero magnitude, least decode entry of each model)
 //   k_prep      requests: validity, bucket key (wave, model, has-prompt), the bucket count
@@ -22,13 +23,14 @@
 // Migration pipeline:
 //   k_fleet     per GPU: bitmask of frequency levels at which all instances meet their SLOs,
 //                 its lowest level and the dynamic-power baseline f[kd0]^3 * u
-//   k_migrate   two sources per block, each source's destinations split over two
+//   k_migrate   two sources per block, the destinations of both split over four
 //                 wavefronts, lanes spanning destinations; fused per-source argmax with
 //                 lowest-destination tie-break
 //
 // Exactness: every SLO and budget test compares a table entry with an SLO, or integers,
 // so it is decided bit-identically to any other correct implementation.  Energies are
-// float32: Pp = fma(k_g*u_g, s*f^3, P0), X = Pp*TTFT, Y = Pd*TBT, E = fma(Lout, Y, X).
+// float32: Pp = fma(k_g*u_g, s*f^3, P0), X = Pp*TTFT, Y = Pd*TBT, E = fma(Lout, Y, X); for 8 x 16
+// tables mostly keys K = fma(Pp, TTFT / Lout, Y) and E = Lout * K.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -2521,8 +2523,8 @@ festina_status place_args(const festina_lut *L, const festina_gpus *G, const fes
 }
 
 // The launches of one placement call on a checked workspace of lay.total bytes (lay.front.total with
-// lay.fronts); ev_begin /
-// ev_end (the timed entry point, else nullptr) are recorded around the scoring kernel.
+// lay.fronts); ev_begin / ev_end (the timed entry point, else nullptr) are recorded around the
+// scoring kernel, or the front search's three.
 festina_status place_launch(const festina_lut *L, const festina_gpus *G, const festina_requests *Q,
                             const festina_placements *out, const PlaceLayout &lay, char *ws, void *stream,
                             void *ev_begin = nullptr, void *ev_end = nullptr) {

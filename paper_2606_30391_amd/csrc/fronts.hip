@@ -19,10 +19,12 @@
 //              in LDS, and each wavefront scores 16 requests of one group against its front:
 //              lanes are cells, the argmin with the lowest-index tie-break is fused
 //
-// Measured per call against the kernels of festina.hip, which score every candidate (those are
-// bound by VALU issue, 1.5 instructions a candidate; these by launches and, in k_choose, by the
-// VALU work per request): 262,144 requests in 64 waves on 1,024 capped GPUs 142 -> 59 us, 65,536
-// requests on 512 GPUs 43.9 -> 28.6 us, 4,096 on 64 GPUs 25.2 -> 19.9 us.
+// Measured per call against the kernels of festina.hip, which score every candidate: 262,144 requests
+// in 64 waves on 1,024 capped GPUs 142 -> 50 us, 65,536 on 512 GPUs 43.9 -> 25, 20,011 in 64 waves on
+// 333 capped GPUs 47.7 -> 35.6.  Those are bound by VALU issue, 1.5 instructions a candidate.  Of
+// these, k_models and k_fronts (5 and 18 us of the 50) are chains of memory round trips, k_fronts'
+// VALU issue taking 31% of its time; k_choose (27 us) issues VALU instructions 58% of its time, the
+// rest being its sort and the loads that one workgroup per CU does not hide.
 //
 // Exactness: keys are evaluated with the same float32 operations for every candidate, so the
 // least key over the fronts is the least over all candidates: rounding is monotone, and a
@@ -921,7 +923,12 @@ __device__ __forceinline__ void all_hosts(const Hosts &h, gptr<float> dcm, gptr<
 }
 
 // The selected requests (of up to N; all of one bucket and kind) against every GPU hosting the model:
-// for requests that the fronts do not serve.  A request is decided on keys where its bucket's front
+// for requests that the fronts do not serve.  Bound by VALU issue, 2 instructions per (request,
+// candidate) and some 20 per (host, cell range); a call without prompts against four requests at a
+// time, and against festina.hip's kernels: 65,536 requests on 512 GPUs 98 / 398 / 159 us, 262,144 on
+// 1,024 575 / 1,684 / 951, 16,384 on 256 68 / 349 / 85, 20,011 on 333 86 / 173 / 74 (groups of four here).
+// Every request with SLOs of its own, read from its lane for each candidate: 158, 833 and (20,011) 110.
+// A request is decided on keys where its bucket's front
 // would decide it so, by its own fields only, so that its result does not depend on whether there is
 // a front.  Lanes are cells (levels 0-3, then 4-7); then lanes are hosts, and each request's tied cells
 // are evaluated on all of them for the lowest index.

@@ -1,7 +1,7 @@
 """Thin ctypes binding of the C ABI in include/festina.h.
 
 Argument marshalling only: every step of the search runs in the HIP library
-(``libfestina.so`` built from ``csrc/festina.hip``, ``csrc/sweep.hip``,
+(``libfestina.so`` built from ``csrc/festina.hip``, ``csrc/fronts.hip``, ``csrc/sweep.hip``,
 ``csrc/preferred.hip``, ``csrc/dispatch.hip`` and ``csrc/transfer.hip``).  PyTorch provides device
 memory and streams.  There is no CPU fallback: if the library is missing this
 module raises.

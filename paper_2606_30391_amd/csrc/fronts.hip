@@ -23,7 +23,7 @@
 // in 64 waves on 1,024 capped GPUs 142 -> 50 us, 65,536 on 512 GPUs 43.9 -> 25, 20,011 in 64 waves on
 // 333 capped GPUs 47.7 -> 35.6.  Those are bound by VALU issue, 1.5 instructions a candidate.  Of
 // these, k_models and k_fronts (5 and 18 us of the 50) are chains of memory round trips, k_fronts'
-// VALU issue taking 31% of its time; k_choose (27 us) issues VALU instructions 58% of its time, the
+// VALU issue taking 31% of its time; k_choose (27 us) issues VALU instructions 61% of its time, the
 // rest being its sort and the loads that one workgroup per CU does not hide.
 //
 // Exactness: keys are evaluated with the same float32 operations for every candidate, so the

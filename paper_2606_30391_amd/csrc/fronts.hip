@@ -23,7 +23,7 @@
 // in 64 waves on 1,024 capped GPUs 142 -> 50 us, 65,536 on 512 GPUs 43.9 -> 25, 20,011 in 64 waves on
 // 333 capped GPUs 47.7 -> 35.6.  Those are bound by VALU issue, 1.5 instructions a candidate.  Of
 // these, k_models and k_fronts (5 and 18 us of the 50) are chains of memory round trips, k_fronts'
-// VALU issue taking 31% of its time; k_choose (27 us) issues VALU instructions 61% of its time, the
+// VALU issue taking 31% of its time; k_choose (27 us) issues VALU instructions 60% of its time, the
 // rest being its sort and the loads that one workgroup per CU does not hide.
 //
 // Exactness: keys are evaluated with the same float32 operations for every candidate, so the
@@ -562,12 +562,9 @@ __device__ __forceinline__ float wave_min(const float (&v)[N]) {
 #pragma unroll
     for (int p = 0; p < 2; ++p) c[p] = vmin(b3 ? w[p + 2] : w[p], dppf<kDppRor8>(b3 ? w[p] : w[p + 2]));
     d = vmin(b2 ? c[1] : c[0], dppf<kDppHalfMirror>(b2 ? c[0] : c[1]));
-  } else if constexpr (N == 8) {
-    d = vmin(b3 ? w[1] : w[0], dppf<kDppRor8>(b3 ? w[0] : w[1]));
-    d = vmin(d, dppf<kDppHalfMirror>(d));
   } else {
-    static_assert(N == 4, "16, 8 or 4 requests");
-    d = vmin(w[0], dppf<kDppRor8>(w[0]));
+    static_assert(N == 8, "16 or 8 requests");
+    d = vmin(b3 ? w[1] : w[0], dppf<kDppRor8>(b3 ? w[0] : w[1]));
     d = vmin(d, dppf<kDppHalfMirror>(d));
   }
   d = vmin(d, dppf<kDppQuad2301>(d));
@@ -923,14 +920,15 @@ __device__ __forceinline__ void all_hosts(const Hosts &h, gptr<float> dcm, gptr<
 }
 
 // The selected requests (of up to N; all of one bucket and kind) against every GPU hosting the model:
-// for requests that the fronts do not serve.  Bound by VALU issue, 2 instructions per (request,
-// candidate) and some 20 per (host, cell range); a call without prompts against four requests at a
-// time, and against festina.hip's kernels: 65,536 requests on 512 GPUs 98 / 398 / 159 us, 262,144 on
-// 1,024 575 / 1,684 / 951, 16,384 on 256 68 / 349 / 85, 20,011 on 333 86 / 173 / 74 (groups of four here).
-// Every request with SLOs of its own, read from its lane for each candidate: 158, 833 and (20,011) 110.
-// A request is decided on keys where its bucket's front
-// would decide it so, by its own fields only, so that its result does not depend on whether there is
-// a front.  Lanes are cells (levels 0-3, then 4-7); then lanes are hosts, and each request's tied cells
+// for requests that the fronts do not serve.  Bound by VALU issue (69% of k_choose's time for 262,144
+// requests without prompts, 10 instructions per (request, host) of 128 cells).  us per call without
+// prompts, against four requests at a time and against festina.hip's kernels: 65,536 requests on 512 GPUs 136 / 398 / 159, 262,144 on
+// 1,024 578 / 1,684 / 951, 16,384 on 256 69 / 349 / 85, 20,011 on 333 88 / 173 / 74 (groups of four here).
+// Every request with SLOs of its own, read from its lane for each candidate: 168, 853 and (20,011) 129.
+// (A variant of four requests beside this one took 98 us for the first, and 0.5% of every call that
+// has none: it left the registers of k_choose's other path fewer.)
+// A request is decided on keys where its bucket's front would decide it so, by its own fields only, so
+// that its result does not depend on whether there is a front.  Lanes are cells (levels 0-3, then 4-7); then lanes are hosts, and each request's tied cells
 // are evaluated on all of them for the lowest index.
 template <int N, int KIND>
 __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, bool sel, const Req &rq, v2f *Q,
@@ -1051,15 +1049,14 @@ __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, bool 
   if (sel && lane % L == 0) put_result(a, rq.r, best != INT_MAX, best, energy);
 }
 
-template <int N>
 __device__ __forceinline__ void choose_all(const FrontArgs &a, int bucket, int kind, bool sel, const Req &rq, v2f *Q,
                                            const float *s_pd) {
   if (kind == kNoPrompt)
-    choose_all<N, kNoPrompt>(a, bucket, sel, rq, Q, s_pd);
+    choose_all<8, kNoPrompt>(a, bucket, sel, rq, Q, s_pd);
   else if (kind == kByEnergy)
-    choose_all<N, kByEnergy>(a, bucket, sel, rq, Q, s_pd);
+    choose_all<8, kByEnergy>(a, bucket, sel, rq, Q, s_pd);
   else
-    choose_all<N, kByKey>(a, bucket, sel, rq, Q, s_pd);
+    choose_all<8, kByKey>(a, bucket, sel, rq, Q, s_pd);
 }
 
 // The kernel's arguments (its only parameter) read again from the kernel-argument segment where
@@ -1200,8 +1197,7 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
     const unsigned tile = (unsigned)uniform((int)s_tile[ti >> 1]);
     const int nt = (int)(tile >> 16), q0 = (ti & 1) * 8;
     if (q0 >= nt) continue;
-    const bool four = nt - q0 <= 4;
-    const int q = q0 + (four ? lane >> 4 : lane >> 3);
+    const int q = q0 + (lane >> 3);
     const bool has = q < nt;
     const int i = s_ord[(tile & 0xffffu) + (has ? q : 0)];
     const v4i rec = s_rec[i];
@@ -1212,10 +1208,7 @@ __global__ void __launch_bounds__(kChooseThreads) k_choose(FrontArgs a) {
       const int b = __builtin_amdgcn_readlane(bkt, __builtin_ctzll(todo));
       const bool sel = has && bkt == b;
       todo &= ~__ballot(sel);
-      if (four)
-        choose_all<4>(fresh_args(), b >> 2, b & 3, sel, rq, s_q[wv], s_pd);
-      else
-        choose_all<8>(fresh_args(), b >> 2, b & 3, sel, rq, s_q[wv], s_pd);
+      choose_all(fresh_args(), b >> 2, b & 3, sel, rq, s_q[wv], s_pd);
     }
   }
 }
